@@ -111,3 +111,42 @@ def test_scratch_kept_between_calls(ks):
     ks.hisq_links(dims, thin, fat, naik)
     torch.cuda.synchronize()
     assert np.array_equal(host(fat), outs[dims][0]) and np.array_equal(host(naik), outs[dims][1])
+
+
+# tiles of 64 sites: a ragged last tile (1296 = 20 * 64 + 16), planes of whole tiles in columns of
+# 4 x 4, 2 x 3 and 1 x 2 tiles, planes that hold no whole tile
+@pytest.mark.parametrize("dims", [(6, 6, 6, 6), (16, 16, 8, 4), (16, 8, 6, 4), (8, 8, 10, 6),
+                                  (4, 12, 4, 10)])
+def test_hisq_tile_orders_match_oracle(ks, dims):
+    announce("hisq tile order", dims)
+    U = thin_links(dims, 0.5, 125)
+    fat, naik = build(ks, dims, U)
+    ofat, onaik = hisq.hisq_links(U, dims)
+    assert np.max(np.abs(fat - ofat)) <= 1e-11 * np.max(np.abs(ofat))
+    assert np.max(np.abs(naik - onaik)) <= 1e-11 * np.max(np.abs(onaik))
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 16, 16), (14, 10, 18, 16)])
+def test_hisq_one_direction_per_pass(ks, dims):
+    """With room for 14 scratch fields but not for 32 the directions take a pass each; every
+    link is formed by the same operations, so the results are equal bit for bit."""
+    import torch
+    announce("hisq small scratch", dims)
+    U = thin_links(dims, 0.5, 126)
+    thin = dev(U.reshape(-1))
+    fat, naik = torch.empty_like(thin), torch.empty_like(thin)
+    ks.hisq_links(dims, thin, fat, naik)
+    fat2, naik2 = torch.empty_like(thin), torch.empty_like(thin)
+    ks.hisq_release()
+    torch.cuda.empty_cache()
+    field = int(np.prod(dims)) * 144
+    free = torch.cuda.mem_get_info()[0]
+    filler = torch.empty(free - 23 * field, dtype=torch.uint8, device="cuda")
+    ks.hisq_links(dims, thin, fat2, naik2)
+    torch.cuda.synchronize()
+    left = torch.cuda.mem_get_info()[0]
+    ks.hisq_release()
+    del filler
+    torch.cuda.empty_cache()
+    assert left >= 5 * field        # the 32 fields were not there to take
+    assert torch.equal(fat, fat2) and torch.equal(naik, naik2)
