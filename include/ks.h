@@ -151,7 +151,9 @@ ks_status_t ks_dslash_eo(ks_gauge_t g, ks_field_t out, ks_field_t in, ks_recon_t
 /* Autotuner: times the Dslash of precision `prec` / Naik storage `recon` on this lattice
  * over candidate launch configurations (64, 128 or 256 threads per block; blocks per CU
  * capped through the LDS request) and keeps the fastest for every later launch through this
- * handle (ks_dslash_eo and the solvers).  Untuned variants use 256 threads, no cap.  Allocates
+ * handle (ks_dslash_eo and the solvers).  Untuned variants use 256 threads and no cap, on small
+ * lattices with four or eight lanes per output site (a form that the tuner also times and that
+ * has no field in ks_dslash_launch; a configuration set by hand has one thread per site).  Allocates
  * two scratch fields for the duration of the call; synchronises the stream.  Must not be
  * called while the stream is being captured into a graph.
  * With the environment variable KS_TUNE_CACHE naming a file, the configuration is taken from

@@ -24,6 +24,8 @@ namespace ks {
 
 namespace {
 
+constexpr int kSplitThreads = 256;   // threads per block of the split form
+
 template <class R>
 __device__ __forceinline__ void matvec_acc(cx<R> acc[3], const cx<R> m[9], const cx<R> v[3])
 {
@@ -217,6 +219,123 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void ds
     }
 }
 
+// Split form: S lanes per output site, each taking 16 / S of its matrices, added by butterflies over
+// the S lanes.  For lattices whose sites are too few waves to fill the chip: there a launch of
+// the one-thread-per-site form lasts as long as one thread's chain of 16 dependent passes
+// (FP64 18-real: 8^4 10.6 us a launch, 12^4 19.3), while here all of a lane's link and vector
+// loads are in flight together (4.6 and 6.0 us with four lanes, 3.7 and 6.2 with eight; 16^4
+// 23.9 -> 12.8).  A wave's loads of one link row are segments of 64 / S sites instead of 64,
+// which costs nothing from the caches but up to 10 % once the links stream from HBM.
+// Lane (64 / S) j + i of a wave works on site i of the wave's 64 / S and on the slots j, j + S,
+// j + 2 S, ...; slot = mu + 4 (backward) + 8 (Naik).
+template <int S, class R>
+__device__ __forceinline__ R split_sum(R v)
+{
+#pragma unroll
+    for (int o = 64 / S; o < 64; o *= 2) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+template <int P, int RECON, bool XPAY, int S>
+__global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
+    Geom g, int par, const void* __restrict__ fat, const void* __restrict__ naik,
+    const void* __restrict__ in, void* __restrict__ out, const void* __restrict__ xv, double a,
+    double* __restrict__ partials, const int* __restrict__ gate, float fat_scale, float naik_scale,
+    double naik_c0)
+{
+    using R = typename St<P>::R;
+    static_assert(S == 4 || S == 8, "a lane's slots j + S u lie in one half of the 16 for each u");
+    constexpr int kSites = 64 / S;                       // per wave
+    constexpr int kBlockSites = kSplitThreads / S;
+    // the gate's load overlaps the others: a launch that it stops has read links for nothing,
+    // one that it lets through does not wait for it first
+    const int stop = gate ? *gate : 0;
+    const int lane = threadIdx.x & 63;
+    const int j = lane / kSites;
+    const int vh = g.Vh;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int hh = tile * kBlockSites + (threadIdx.x >> 6) * kSites + lane % kSites;
+    const bool live = hh < vh;
+    const int h = live ? hh : vh - 1;                    // a dead lane shadows a live site
+    int c[4];
+    cb_coords(g, h, par, c);
+    const int i = site_index(g, c);
+    cx<R> xs[3];
+    if (XPAY) Spinor<P>::load(xv, vh, h, xs);
+    cx<R> res[3] = {{0, 0}, {0, 0}, {0, 0}};
+    constexpr int K = 16 / S;
+    cx<R> m[K][9], v[K][3];
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const int s = j + S * u;
+        const int mu = s & 3;
+        const int cm = mu == 0 ? c[0] : mu == 1 ? c[1] : mu == 2 ? c[2] : c[3];
+        const int n = mu == 0 ? g.n[0] : mu == 1 ? g.n[1] : mu == 2 ? g.n[2] : g.n[3];
+        const int st = mu == 0 ? 1 : mu == 1 ? g.stride[1] : mu == 2 ? g.stride[2] : g.stride[3];
+        const int d = (s & 8 ? 3 : 1) * (s & 4 ? -1 : 1);
+        const int q = cm + d;
+        const int nb = (i + (d + (q < 0 ? n : 0) - (q >= n ? n : 0)) * st) >> 1;
+        if (RECON == 18) load_link<P, 9>(S * u < 8 ? fat : naik, s & 7, g.lp, h, m[u]);
+        else if (S * u < 8) load_link<P, 9>(fat, s, g.lp, h, m[u]);
+        else load_link<P, 6>(naik, s - 8, g.lp, h, m[u]);
+        Spinor<P>::load(in, vh, nb, v[u]);
+    }
+    // every load is issued before the first of their values is used (left to itself the
+    // compiler puts each behind the arithmetic of the one before: 16^4 FP64 17.1 us, not 12.8)
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+#pragma unroll
+        for (int e = 0; e < (RECON == 12 && S * u >= 8 ? 6 : 9); ++e)
+            asm volatile("" : "+v"(m[u][e].r), "+v"(m[u][e].i));
+#pragma unroll
+        for (int e = 0; e < 3; ++e) asm volatile("" : "+v"(v[u][e].r), "+v"(v[u][e].i));
+    }
+    if (stop) return;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const int s = j + S * u;
+        R sc = (R)(S * u < 8 ? fat_scale : naik_scale);
+        if (RECON == 12 && S * u >= 8) {
+            reconstruct_row2(m[u]);
+            sc = (R)(naik_c0 * naik_sign(c, s - 8, g.n[3]));
+        }
+        cx<R> t[3] = {{0, 0}, {0, 0}, {0, 0}};
+        matvec_acc(t, m[u], v[u]);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            res[b].r = fma(sc, t[b].r, res[b].r);
+            res[b].i = fma(sc, t[b].i, res[b].i);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        res[b].r = split_sum<S>(res[b].r);
+        res[b].i = split_sum<S>(res[b].i);
+    }
+    double dot = 0.0;
+    if (XPAY) {
+        const R aa = (R)a;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            res[k].r = aa * xs[k].r - res[k].r;
+            res[k].i = aa * xs[k].i - res[k].i;
+        }
+    }
+    if (live && j == 0) {
+        Spinor<P>::store(out, vh, h, res);
+        if (XPAY && partials) {
+            Spinor<P>::round(res);       // Re<x, out> of the output as stored
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                dot += (double)xs[k].r * (double)res[k].r + (double)xs[k].i * (double)res[k].i;
+        }
+    }
+    if (XPAY && partials) {
+        const double sum = block_sum<kSplitThreads>(dot);
+        if (threadIdx.x == 0) partials[tile] = sum;
+    }
+}
+
 // dynamic LDS of the staged form: the block's sites and the x/y halo on both sides
 int staged_lds_bytes(int P, int NT, const Geom& G)
 {
@@ -256,6 +375,35 @@ void launch_g(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a
     }
 }
 
+// Lanes per site of a launch: what the tuner found (or 1 for a configuration set by hand), else by
+// size.  Where the lines lie, us per launch one / four / eight lanes (18-real; 12-real alike):
+//   eight: 8^4 FP64 10.6 / 4.6 / 3.7, FP32 7.4 / 3.9 / 3.3, FP16 10.1 / 3.7 / 3.5;
+//          12^4 FP64 19.3 / 6.0 / 6.2, FP32 13.0 / 4.9 / 5.1;
+//   four:  FP64 20^4 38.3 / 32.5, 24^4 68.9 / 72.7; FP32 20^4 18.8 / 15.1, 24^4 33.3 / 33.8;
+//          FP16 24^4 18.4 / 17.5 (12-real 22.5 / 16.7), 28^4 31.1 / 34.6.
+int split_of(const TuneEntry& t, int P, int vh)
+{
+    if (t.split > 0) return t.split;
+    if (vh <= 4096) return 8;
+    return vh <= (P == KS_F64 ? 100000 : P == KS_F32 ? 130000 : 200000) ? 4 : 1;
+}
+
+template <int P, int RECON, int S>
+void launch_split(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a, hipStream_t s)
+{
+    const int nb = blocks_for(G.Vh, kSplitThreads / S);
+    const int p = a.out_parity;
+    if (a.x)
+        dslash_split_kernel<P, RECON, true, S><<<nb, kSplitThreads, 0, s>>>(
+            G, p, st.fat[p], st.naik[p], a.in, a.out, a.x, a.a, a.dot_partials, a.gate,
+            st.fat_scale, st.naik_scale, c0);
+    else
+        dslash_split_kernel<P, RECON, false, S><<<nb, kSplitThreads, 0, s>>>(
+            G, p, st.fat[p], st.naik[p], a.in, a.out, nullptr, 0.0, nullptr, a.gate, st.fat_scale,
+            st.naik_scale, c0);
+    KS_HIP(hipGetLastError());
+}
+
 template <int P, int RECON, int NT, int U>
 void launch_u(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a,
               const TuneEntry& t, hipStream_t s)
@@ -282,6 +430,15 @@ template <int P, int RECON>
 void launch_p(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a,
               const TuneEntry& t, hipStream_t s)
 {
+    const int split = split_of(t, P, G.Vh);
+    if (split == 4) {
+        launch_split<P, RECON, 4>(st, G, c0, a, s);
+        return;
+    }
+    if (split == 8) {
+        launch_split<P, RECON, 8>(st, G, c0, a, s);
+        return;
+    }
     if (t.nt == 64) launch_nt<P, RECON, 64>(st, G, c0, a, t, s);
     else if (t.nt == 128) launch_nt<P, RECON, 128>(st, G, c0, a, t, s);
     else launch_nt<P, RECON, 256>(st, G, c0, a, t, s);
@@ -305,7 +462,9 @@ void launch(ks_gauge_t g, ks_prec_t prec, int ri, const DslashArgs& a, const Tun
 
 int dslash_blocks(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon)
 {
-    return blocks_for(g->geom.Vh, g->tune[prec][recon_index(recon)].nt);
+    const TuneEntry& t = g->tune[prec][recon_index(recon)];
+    const int split = split_of(t, (int)prec, g->geom.Vh);
+    return blocks_for(g->geom.Vh, split > 1 ? kSplitThreads / split : t.nt);
 }
 
 bool dslash_form_built(ks_prec_t prec, ks_recon_t recon, int links_per_pass, int link_access,
@@ -315,7 +474,7 @@ bool dslash_form_built(ks_prec_t prec, ks_recon_t recon, int links_per_pass, int
            form_built((int)prec, (int)recon, links_per_pass, link_access == 4, staged != 0);
 }
 
-int dslash_max_blocks(const Geom& g) { return blocks_for(g.Vh, 64); }
+int dslash_max_blocks(const Geom& g) { return blocks_for(g.Vh, kSplitThreads / 8); }
 
 void dslash(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, const DslashArgs& a, hipStream_t s)
 {
@@ -369,9 +528,9 @@ std::string cache_line(const CacheKey& k, const TuneEntry& t)
     std::snprintf(b, sizeof(b),
                   "{\"arch\": \"%s\", \"cus\": %d, \"dims\": [%d, %d, %d, %d], \"prec\": %d, "
                   "\"naik\": %d, \"threads\": %d, \"lds_bytes\": %d, \"links_per_pass\": %d, "
-                  "\"link_access\": %d, \"staged\": %d, \"us\": %.2f}",
+                  "\"link_access\": %d, \"staged\": %d, \"us\": %.2f, \"split\": %d}",
                   k.arch.c_str(), k.cus, k.dims[0], k.dims[1], k.dims[2], k.dims[3], k.prec, k.naik,
-                  t.nt, t.lds, t.group, t.way, t.staged, (double)t.us);
+                  t.nt, t.lds, t.group, t.way, t.staged, (double)t.us, t.split);
     return b;
 }
 
@@ -383,10 +542,14 @@ bool parse_line(const std::string& line, CacheKey& k, TuneEntry& t)
         line.c_str(),
         "{\"arch\": \"%63[^\"]\", \"cus\": %d, \"dims\": [%d, %d, %d, %d], \"prec\": %d, "
         "\"naik\": %d, \"threads\": %d, \"lds_bytes\": %d, \"links_per_pass\": %d, "
-        "\"link_access\": %d, \"staged\": %d, \"us\": %f}",
+        "\"link_access\": %d, \"staged\": %d, \"us\": %f, \"split\": %d}",
         arch, &k.cus, &k.dims[0], &k.dims[1], &k.dims[2], &k.dims[3], &k.prec, &k.naik, &t.nt,
-        &t.lds, &t.group, &t.way, &t.staged, &us);
-    if (n != 14) return false;
+        &t.lds, &t.group, &t.way, &t.staged, &us, &t.split);
+    if (n < 14) return false;
+    // an entry without the last field, or edited to a form that the split one does not have
+    if (n == 14 || t.way != 8 || t.staged || t.group != 1 || t.nt != kSplitThreads || t.lds != 0 ||
+        (t.split != 4 && t.split != 8))
+        t.split = 1;
     k.arch = arch;
     t.us = us;
     return true;
@@ -503,6 +666,12 @@ void dslash_tune(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t s)
         a.out_parity = 0;
         a.in = in;
         a.out = out;
+        for (int split : {4, 8}) {
+            TuneEntry t;
+            t.split = split;
+            for (int k = 0; k < 2; ++k) launch(g, prec, ri, a, t, s);
+            timed.push_back({time_launches(g, prec, ri, a, t, 5, e0, e1, s), t});
+        }
         for (int staged : {0, 1}) {
         for (int way : {8, 4}) {
         for (int group : {1, 2, 4}) {
@@ -510,6 +679,7 @@ void dslash_tune(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t s)
         for (int nt : {64, 128, 256}) {
             for (int blocks_cu : {0, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}) {
                 TuneEntry t;
+                t.split = 1;
                 t.nt = nt;
                 t.group = group;
                 t.way = way;
@@ -557,10 +727,10 @@ void dslash_tune(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t s)
     best.tuned = true;
     g->tune[prec][ri] = best;
     log_msg(1, "tuned %s %d-real Dslash at %dx%dx%dx%d: %d threads, %d links per pass, %d-way, "
-               "%s gathers, %d B LDS, %.1f us",
+               "%s gathers, %d B LDS, %d lanes per site, %.1f us",
             prec == KS_F64 ? "FP64" : prec == KS_F32 ? "FP32" : "FP16", naik, G.n[0], G.n[1],
             G.n[2], G.n[3], best.nt, best.group, best.way, best.staged ? "staged" : "cached",
-            best.lds, (double)best_us);
+            best.lds, best.split, (double)best_us);
     if (cache && *cache) cache_store(cache, key, best);
 }
 

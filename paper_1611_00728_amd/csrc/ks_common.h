@@ -92,6 +92,7 @@ struct TuneEntry {
     int group = 1;      // link matrices loaded per pass of the Dslash site loop
     int way = 8;        // 8: a site's own backward slots; 4: neighbours' forward slots
     int staged = 0;     // 1: x/y neighbour vectors staged in LDS
+    int split = 0;      // lanes per site; 0: by the lattice's size
     int lds = 0;
     float us = 0.f;     // measured time per launch when tuned
     bool tuned = false;

@@ -305,3 +305,54 @@ def test_tune_cache(ks, tmp_path, monkeypatch):
     assert len(lines) == 3 and sorted(json.loads(x)["prec"] for x in lines[1:]) == [0, 1]
     for G in (G1, G2, G3):
         G.free()
+
+
+# lattices of few sites take several lanes per output site: eight up to 4096 sites, then four;
+# ragged last waves and blocks (648 = 20 * 32 + 8, 4200 = 65 * 64 + 40)
+@pytest.mark.parametrize("dims", [(6, 6, 6, 6), (8, 8, 8, 16), (6, 10, 14, 10)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("recon", [18, 12])
+def test_dslash_lanes_per_site(ks, dims, prec, recon):
+    """The size-chosen form against the oracle, element by element, and the tuned one (which may
+    be either form) against the same bound."""
+    announce("dslash lanes per site", dims, prec, recon)
+    g = make_gauge(dims, 0.5, 4)
+    G = ks.Gauge(dims, g.fat, g.naik)
+    vh = g.volume // 2
+    P = ks.PREC[prec]
+    for tuned in (False, True):
+        access = G.tune(P, recon)["link_access"] if tuned else 8
+        for out_par in (0, 1):
+            psi = gaussian_source(vh, 500 + out_par)
+            got = run_dslash(ks, G, vh, out_par, psi, P, recon)
+            ref, S = dc.reference(g, prec, recon, access, out_par, psi)
+            assert dc.worst(got, ref, S, prec) <= 1.0
+
+
+def test_tune_cache_keeps_lanes_per_site(ks, tmp_path, monkeypatch):
+    """An entry with several lanes per site is taken as written; one edited to a form that has
+    one thread per site only, and one without the field, take that form."""
+    import json
+    announce("tune cache lanes per site")
+    path = tmp_path / "tune.jsonl"
+    monkeypatch.setenv("KS_TUNE_CACHE", str(path))
+    dims = (8, 8, 8, 8)
+    g = make_gauge(dims, 0.5, 3)
+    vh = g.volume // 2
+    ks.Gauge(dims, g.fat, g.naik).tune(ks.F32, 18)
+    e = json.loads(path.read_text())
+    assert e["split"] in (1, 4, 8)
+    e.update(threads=256, lds_bytes=0, links_per_pass=1, link_access=8, staged=0, us=1.5)
+    old = {k: v for k, v in e.items() if k != "split"}
+    psi = gaussian_source(vh, 809)
+    ref, S = dc.reference(g, "f32", 18, 8, 1, psi)
+    outs = []
+    for entry in (dict(e, split=4), dict(e, split=8), dict(e, split=8, threads=128), old):
+        path.write_text(json.dumps(entry) + "\n")
+        G = ks.Gauge(dims, g.fat, g.naik)
+        assert G.tune(ks.F32, 18)["tuned_us"] == pytest.approx(1.5)
+        assert G.config(ks.F32, 18)["threads"] == entry["threads"]
+        outs.append(run_dslash(ks, G, vh, 1, psi, ks.F32, 18))
+        assert dc.worst(outs[-1], ref, S, "f32") <= 1.0
+    # one thread per site adds in one order whatever the block
+    assert np.array_equal(outs[2], outs[3])
