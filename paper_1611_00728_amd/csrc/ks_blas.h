@@ -35,12 +35,16 @@ void sub_norm_partials(int vh, const double* b, const double* ax, double* r, dou
                        hipStream_t s);
 // x (FP64 planes) += dx (FP32 field); dx = 0
 void flush_dx(int vh, void* dx, double* x, hipStream_t s);
-// Threads per block of the two fused CG step kernels (one site per thread).
+// Threads per block of the two fused CG step kernels (one site per thread): 1024, so that there
+// are few partials for every block to add up, but 256 on lattices of up to kCgSmall sites,
+// which 1024 would leave on few CUs.
 constexpr int kCgFuse = 1024;
+constexpr int kCgSmall = 131072;
+int cg_step_threads(int vh);
 // One CG step after q = A p and the <p, q> partials (npap of them) are written: every block
 // sums the partials in the same order and takes alpha = rho / <p, q>; then x += alpha p (x:
 // FP64 planes, or in reduced precision x's FP32 increment field, see flush_dx),
-// r -= alpha q, and the |r|^2 partials to rr_part (blocks_for(vh, kCgFuse) of them).
+// r -= alpha q, and the |r|^2 partials to rr_part (blocks_for(vh, cg_step_threads(vh)) of them).
 // Breakdown and a non-finite <p, q> gate the solver.  Step k's alpha goes to coef[2k]
 // (k < coef_cap).
 void cg_update(int vh, ks_prec_t prec, void* x, const void* p, const void* q, void* r,

@@ -165,12 +165,39 @@ __device__ __forceinline__ int site_index(const Geom& g, const int c[4])
     return c[0] + g.stride[1] * c[1] + g.stride[2] * c[2] + g.stride[3] * c[3];
 }
 
-// Wave + block sum of a double into one value per block (thread 0 holds it).
+// v of the lane that the DPP control kCtrl names (within the 16 lanes of a row)
+template <int kCtrl>
+__device__ __forceinline__ double dpp_lane(double v)
+{
+    int w[2];
+    __builtin_memcpy(w, &v, 8);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) w[k] = __builtin_amdgcn_update_dpp(0, w[k], kCtrl, 0xf, 0xf, true);
+    __builtin_memcpy(&v, w, 8);
+    return v;
+}
+
+__device__ __forceinline__ double read_lane(double v, int lane)
+{
+    int w[2];
+    __builtin_memcpy(w, &v, 8);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) w[k] = __builtin_amdgcn_readlane(w[k], lane);
+    __builtin_memcpy(&v, w, 8);
+    return v;
+}
+
+// Sum over the wave's 64 lanes (all of them active), the same value in every lane: within a row
+// of 16 by register-to-register lane moves (neighbours, pairs, half rows, rows), then the four
+// rows by lane reads.  Six exchanges through the LDS crossbar instead take some 0.3 us, which
+// a CG step on a small lattice spends five times.
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v += dpp_lane<0xB1>(v);     // quad_perm 1, 0, 3, 2
+    v += dpp_lane<0x4E>(v);     // quad_perm 2, 3, 0, 1
+    v += dpp_lane<0x141>(v);    // row_half_mirror
+    v += dpp_lane<0x140>(v);    // row_mirror
+    return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
 __device__ __forceinline__ double wave_max(double v)

@@ -12,7 +12,7 @@ struct Workspace {
     size_t bytes = 0;
     int npart = 0;
     double* partials = nullptr;   // per-block partial sums
-    double* rr_part = nullptr;    // |r|^2 partials of the fused CG step (blocks_for(Vh, kCgFuse))
+    double* rr_part = nullptr;    // |r|^2 partials of the fused CG step (blocks_for(Vh, cg_step_threads(Vh)))
     double* cg_coef = nullptr;    // alpha_k, beta_k of the last CG run, interleaved
     int cg_coef_cap = 0;          // steps it holds
     int cg_coef_n = 0;            // steps recorded by the last run

@@ -58,7 +58,7 @@ Workspace& workspace(ks_gauge_t g)
         w.partials = static_cast<double*>(device_alloc(sizeof(double) * (cap + 64)));
         w.scal = w.partials + cap;
         w.bytes += sizeof(double) * (cap + 64);
-        const int nrr = blocks_for(vh, kCgFuse);
+        const int nrr = blocks_for(vh, cg_step_threads(vh));
         w.rr_part = static_cast<double*>(device_alloc(sizeof(double) * nrr));
         w.bytes += sizeof(double) * nrr;
         w.st = static_cast<CGState*>(device_alloc(sizeof(CGState)));

@@ -391,3 +391,27 @@ def test_ks_log_solve_summary(ks):
     assert "[ks] tuned FP32 18-real Dslash at 4x4x4x8:" in out.stderr
     line = [l for l in out.stderr.splitlines() if l.startswith("[ks] cg: ")]
     assert len(line) == 1 and line[0].startswith("[ks] cg: status 0, %d steps," % iters)
+
+
+# 256 and 1024 threads per block in the fused CG step kernels (line at 131072 sites), a ragged last
+# block in both (131712 = 514 * 256 + 128, 128.6 * 1024)
+@pytest.mark.parametrize("dims", [(6, 6, 6, 6), (24, 28, 14, 28), (16, 16, 32, 32)])
+def test_cg_step_blocks(ks, dims):
+    """A few CG steps with each block size take the oracle's path: after 6 steps (no reliable
+    update at delta = 0) x is the oracle's CG iterate to the inner precision's rounding
+    (2^-40, 2^-16, 2^-7 of |x|: a few hundred ulps of the format over 6 well-conditioned steps)."""
+    import torch
+    g = make_gauge(dims, 0.3, 91)
+    G = ks.Gauge(dims, g.fat, g.naik)
+    vh = g.volume // 2
+    b = gaussian_source(vh, 92)
+    ref, _ = oracle.cg(g, 4.0, b, 1e-30, max_iter=6, max_restarts=0)
+    for inner, tol in (("f64", 2.0 ** -40), ("f32", 2.0 ** -16), ("f16", 2.0 ** -7)):
+        announce("cg step blocks", dims, inner)
+        x = zeros_dev((vh, 3))
+        res = ks.cg_solve(G, 1.0, dev(b), x, ks.default_params(tol=1e-30, max_iter=6, delta=0.0,
+                                                              inner=ks.PREC[inner]),
+                          raise_on_error=False)
+        torch.cuda.synchronize()
+        assert res.stats["iters"] == 6
+        assert np.linalg.norm(host(x) - ref) <= tol * np.linalg.norm(ref)
