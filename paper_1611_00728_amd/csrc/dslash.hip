@@ -236,7 +236,7 @@ __device__ __forceinline__ R split_sum(R v)
     return v;
 }
 
-template <int P, int RECON, bool XPAY, int S>
+template <int P, int RECON, bool XPAY, int S, bool kStream>
 __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
     Geom g, int par, const void* __restrict__ fat, const void* __restrict__ naik,
     const void* __restrict__ in, void* __restrict__ out, const void* __restrict__ xv, double a,
@@ -275,9 +275,9 @@ __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
         const int d = (s & 8 ? 3 : 1) * (s & 4 ? -1 : 1);
         const int q = cm + d;
         const int nb = (i + (d + (q < 0 ? n : 0) - (q >= n ? n : 0)) * st) >> 1;
-        if (RECON == 18) load_link<P, 9>(S * u < 8 ? fat : naik, s & 7, g.lp, h, m[u]);
-        else if (S * u < 8) load_link<P, 9>(fat, s, g.lp, h, m[u]);
-        else load_link<P, 6>(naik, s - 8, g.lp, h, m[u]);
+        if (RECON == 18) load_link<P, 9, kStream>(S * u < 8 ? fat : naik, s & 7, g.lp, h, m[u]);
+        else if (S * u < 8) load_link<P, 9, kStream>(fat, s, g.lp, h, m[u]);
+        else load_link<P, 6, kStream>(naik, s - 8, g.lp, h, m[u]);
         Spinor<P>::load(in, vh, nb, v[u]);
     }
     // every load is issued before the first of their values is used (left to itself the
@@ -388,17 +388,23 @@ int split_of(const TuneEntry& t, int P, int vh)
     return vh <= (P == KS_F64 ? 100000 : P == KS_F32 ? 130000 : 200000) ? 4 : 1;
 }
 
-template <int P, int RECON, int S>
+// Links of both parities up to this size are read through the caches: the last-level one (256 MB)
+// then still holds them, beside the vectors, at a solver's next step; larger ones are streamed.
+// CG step, streamed / through the caches: 186 MB (14x18x16x20 FP64) 48.7 / 43.0 us, 184 MB (20^4
+// FP32) 56.4 / 53.3, 133 MB (24^3x20 FP16 12-real) 56.5 / 52.8; 369 MB (20^4 FP64) 82.8 / 88.6.
+constexpr size_t kCachedLinks = (size_t)200 << 20;
+
+template <int P, int RECON, int S, bool kStream>
 void launch_split(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a, hipStream_t s)
 {
     const int nb = blocks_for(G.Vh, kSplitThreads / S);
     const int p = a.out_parity;
     if (a.x)
-        dslash_split_kernel<P, RECON, true, S><<<nb, kSplitThreads, 0, s>>>(
+        dslash_split_kernel<P, RECON, true, S, kStream><<<nb, kSplitThreads, 0, s>>>(
             G, p, st.fat[p], st.naik[p], a.in, a.out, a.x, a.a, a.dot_partials, a.gate,
             st.fat_scale, st.naik_scale, c0);
     else
-        dslash_split_kernel<P, RECON, false, S><<<nb, kSplitThreads, 0, s>>>(
+        dslash_split_kernel<P, RECON, false, S, kStream><<<nb, kSplitThreads, 0, s>>>(
             G, p, st.fat[p], st.naik[p], a.in, a.out, nullptr, 0.0, nullptr, a.gate, st.fat_scale,
             st.naik_scale, c0);
     KS_HIP(hipGetLastError());
@@ -431,12 +437,15 @@ void launch_p(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a
               const TuneEntry& t, hipStream_t s)
 {
     const int split = split_of(t, P, G.Vh);
+    const size_t links = (size_t)2 * 8 * (9 + (RECON == 12 ? 6 : 9)) * EntrySize<P>::value * G.lp;
     if (split == 4) {
-        launch_split<P, RECON, 4>(st, G, c0, a, s);
+        if (links <= kCachedLinks) launch_split<P, RECON, 4, false>(st, G, c0, a, s);
+        else launch_split<P, RECON, 4, true>(st, G, c0, a, s);
         return;
     }
     if (split == 8) {
-        launch_split<P, RECON, 8>(st, G, c0, a, s);
+        if (links <= kCachedLinks) launch_split<P, RECON, 8, false>(st, G, c0, a, s);
+        else launch_split<P, RECON, 8, true>(st, G, c0, a, s);
         return;
     }
     if (t.nt == 64) launch_nt<P, RECON, 64>(st, G, c0, a, t, s);

@@ -108,8 +108,16 @@ struct LinkPack {
     }
 };
 
-// the N entries of link `slot` at site h from planes of lp sites
-template <int P, int N>
+template <bool kStream, class T>
+__device__ __forceinline__ T link_read(const T* p)
+{
+    if constexpr (kStream) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+// the N entries of link `slot` at site h from planes of lp sites.  kStream: read past the caches
+// (links that a launch reads once and that no cache would still hold at the next one)
+template <int P, int N, bool kStream = true>
 __device__ __forceinline__ void load_link(const void* base, int slot, int lp, int h,
                                           cx<typename St<P>::R> m[9])
 {
@@ -119,14 +127,14 @@ __device__ __forceinline__ void load_link(const void* base, int slot, int lp, in
     for (int j = 0; j < LP::NF; ++j) {
         const char* pl = sb + (size_t)j * 16 * lp;
         if constexpr (P == KS_F64) {
-            const dvec2 v = __builtin_nontemporal_load(reinterpret_cast<const dvec2*>(pl) + h);
+            const dvec2 v = link_read<kStream>(reinterpret_cast<const dvec2*>(pl) + h);
             m[j] = {v.x, v.y};
         } else if constexpr (P == KS_F32) {
-            const fvec4 v = __builtin_nontemporal_load(reinterpret_cast<const fvec4*>(pl) + h);
+            const fvec4 v = link_read<kStream>(reinterpret_cast<const fvec4*>(pl) + h);
             m[2 * j] = {v.x, v.y};
             m[2 * j + 1] = {v.z, v.w};
         } else {
-            const uvec4 v = __builtin_nontemporal_load(reinterpret_cast<const uvec4*>(pl) + h);
+            const uvec4 v = link_read<kStream>(reinterpret_cast<const uvec4*>(pl) + h);
             m[4 * j] = half2_to_cx(v.x);
             m[4 * j + 1] = half2_to_cx(v.y);
             m[4 * j + 2] = half2_to_cx(v.z);
@@ -137,13 +145,13 @@ __device__ __forceinline__ void load_link(const void* base, int slot, int lp, in
         const char* pl = sb + (size_t)LP::NF * 16 * lp;
         constexpr int o = LP::NF * LP::W;
         if constexpr (P == KS_F32) {
-            const fvec2 v = __builtin_nontemporal_load(reinterpret_cast<const fvec2*>(pl) + h);
+            const fvec2 v = link_read<kStream>(reinterpret_cast<const fvec2*>(pl) + h);
             m[o] = {v.x, v.y};
         } else if constexpr (P == KS_F16 && LP::NR == 1) {
-            const unsigned v = __builtin_nontemporal_load(reinterpret_cast<const unsigned*>(pl) + h);
+            const unsigned v = link_read<kStream>(reinterpret_cast<const unsigned*>(pl) + h);
             m[o] = half2_to_cx(v);
         } else if constexpr (P == KS_F16 && LP::NR == 2) {
-            const uvec2 v = __builtin_nontemporal_load(reinterpret_cast<const uvec2*>(pl) + h);
+            const uvec2 v = link_read<kStream>(reinterpret_cast<const uvec2*>(pl) + h);
             m[o] = half2_to_cx(v.x);
             m[o + 1] = half2_to_cx(v.y);
         } else {
