@@ -618,7 +618,7 @@ ks_status_t ks_net_apply(ks_net_t n, ks_gauge_t g, const double* in_dev, double*
     KS_REQUIRE(n && n->ctx && g && in_dev && out_dev, KS_ERR_ARG, "ks_net_apply: null argument");
     KS_REQUIRE(in_dev != out_dev, KS_ERR_ARG, "ks_net_apply: out aliases in");
     if (use_mfma) net_apply_mfma(*n->ctx, g, in_dev, out_dev, stream);
-    else net_apply_f32(*n->ctx, g, in_dev, out_dev, 1.0, stream);
+    else net_apply_f32(*n->ctx, g, in_dev, out_dev, stream);
     return KS_SUCCESS;
     KS_API_END
 }

@@ -18,7 +18,7 @@ extern const int kLayerOut[4];
 size_t layer_weight_offset(int l);   // complex offset of layer l's weights
 
 // Activation and gradient buffers of one lattice size: levels 0..4 (channels 1, 8, 8, 8, 1),
-// each [parity][channel][colour][Vh] complex FP32.
+// FP32 as act_pair (8 channels) and ActPlanes (1 channel, even sites) lay them out.
 struct NetBuffers {
     int vh = 0;
     float2* act[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -58,9 +58,7 @@ void net_get_state(NetCtx& n, double* w, double* m, double* v, int* step, hipStr
 void net_set_state(NetCtx& n, const double* w, const double* m, const double* v, int step,
                    hipStream_t s);
 NetBuffers& net_buffers(NetCtx& n, const Geom& g);
-void net_forward(NetCtx& n, NetBuffers& B, ks_gauge_t g, hipStream_t s);
-void net_apply_f32(NetCtx& n, ks_gauge_t g, const double* in, double* out, double in_scale,
-                   hipStream_t s);
+void net_apply_f32(NetCtx& n, ks_gauge_t g, const double* in, double* out, hipStream_t s);
 // complex128 [Vh][3] even-site vectors, on the matrix-core path
 void net_apply_mfma(NetCtx& n, ks_gauge_t g, const double* in, double* out, hipStream_t s);
 // matrix-core operands of the four layers for the current weights and g's binary16 link scale

@@ -42,23 +42,6 @@ constexpr int kWaveSites = 16;     // sites per wave
 constexpr int kBlockSites = 64;    // four waves per block
 constexpr int kFrags = 9;          // A fragments per layer: identity, then (hop j, pair cp)
 
-// complex128 site-major vectors [Vh][3] (the network's own entry point)
-struct SpinorAos {
-    using R = double;
-    __device__ static __forceinline__ void load(const void* b, int, int h, cx<R> v[3])
-    {
-        const double2* p = static_cast<const double2*>(b) + (size_t)3 * h;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) v[k] = {p[k].x, p[k].y};
-    }
-    __device__ static __forceinline__ void store(void* b, int, int h, const cx<R> v[3])
-    {
-        double2* p = static_cast<double2*>(b) + (size_t)3 * h;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) p[k] = make_double2(v[k].r, v[k].i);
-    }
-};
-
 __device__ __forceinline__ half2_t as_h2(unsigned u)
 {
     half2_t h;
@@ -124,26 +107,6 @@ __global__ void net_frag_kernel(const float2* __restrict__ w, int cin, int cout,
         v[i] = (_Float16)a;
     }
     frag[f * 64 + l] = v;
-}
-
-// Checkerboard row of the site k steps along mu = g (lane-dependent) from site i.  The extents
-// and strides pass through readfirstlane (they are uniform) so that the per-lane choice stays a
-// select between registers, not an indexed read of the kernel argument from scratch memory.
-__device__ __forceinline__ int lane_hop(const Geom& geo, int i, const int c[4], int g, int k)
-{
-    int ext[4], str[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        ext[d] = __builtin_amdgcn_readfirstlane(geo.n[d]);
-        str[d] = __builtin_amdgcn_readfirstlane(geo.stride[d]);
-    }
-    const int cm = (g == 0 ? c[0] : g == 1 ? c[1] : g == 2 ? c[2] : c[3]) + k;
-    const int n = g == 0 ? ext[0] : g == 1 ? ext[1] : g == 2 ? ext[2] : ext[3];
-    const int st = g == 0 ? str[0] : g == 1 ? str[1] : g == 2 ? str[2] : str[3];
-    int j = i + k * st;
-    if (cm >= n) j -= n * st;
-    else if (cm < 0) j += n * st;
-    return j >> 1;
 }
 
 // The nine entries of stored link slot s at checkerboard row h (binary16 (re, im) pairs, planes

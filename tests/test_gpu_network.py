@@ -393,3 +393,70 @@ def test_trained_network_cuts_iterations(ks):
     assert iters["fcg"] <= 0.7 * iters["cg"], iters
     net.free()
     G.free()
+
+
+# 16-site groups per wave: two with a ragged last wave (14^4: 2401 groups), and one with lanes past
+# the end and both parities in a group (7920 sites, 3960 of each)
+@pytest.mark.parametrize("dims", [(14, 14, 14, 14), (10, 6, 6, 22)])
+def test_forward_f32_groups(ks, dims):
+    announce("net forward groups", dims)
+    import torch
+    g = make_gauge(dims, 0.5, 79)
+    G = ks.Gauge(dims, g.fat, g.naik)
+    ws = random_net(5002)
+    net = ks.Net(flatten_weights(ws))
+    b = gaussian_source(g.volume // 2, 4)
+    ref, _ = N.network_forward(N.Network(ws), g, b, keep_cache=False)
+    out = zeros_dev(b.shape)
+    net.apply(G, dev(b), out, mfma=False)
+    torch.cuda.synchronize()
+    assert rel_l2(host(out), ref) <= 1e-5
+    assert np.all(np.abs(host(out) - ref) <= 2.0 ** -13 * modulus_sums(g, ws, b))
+
+
+# ragged tiles of 64 sites (648 = 10 * 64 + 8 even sites), less than one tile (32 even sites of
+# (4, 4, 4, 4) are half of one), and links read past the caches (over 100 MB: 184320 sites)
+@pytest.mark.parametrize("dims", [(6, 6, 6, 6), (4, 4, 4, 4), (24, 24, 20, 16)])
+def test_gradient_tiles(ks, dims):
+    announce("net gradient tiles", dims)
+    g = make_gauge(dims, 0.4, 82)
+    x = gaussian_source(g.volume // 2, 84)
+    sig = 0.3
+    b = oracle.apply_A(g, sig, x)              # a pair of the form that training has: A x = b
+    G = ks.Gauge(dims, g.fat, g.naik)
+    ws = random_net(5003)
+    loss, grad = ks.Net(flatten_weights(ws)).loss_grad([G], [sig], [dev(b)], [dev(x)])
+    l, gr = N.loss_and_grad(N.Network([w.copy() for w in ws]), g, [sig], [b], [x])
+    rg = flatten_weights(gr)
+    assert abs(loss - l) <= 1e-5 * l
+    assert rel_l2(grad, rg) <= 1e-4
+    assert np.max(np.abs(grad - rg)) <= 1.5e-4 * np.max(np.abs(rg))
+
+
+def test_gradient_of_many_pairs(ks):
+    """Over 32 pairs, whose scalars the host reads 32 at a time: loss and gradient are the mean of
+    the pairs' own (each is divided by the number of pairs in FP64; the gradients meet in FP64
+    after FP32 passes of their own scale: 1e-5), and a pair with Re<x, b> <= 0 is refused
+    wherever it stands."""
+    announce("net many pairs")
+    dims = (4, 4, 4, 6)
+    g = make_gauge(dims, 0.4, 85)
+    G = ks.Gauge(dims, g.fat, g.naik)
+    net = ks.Net(flatten_weights(random_net(5004)))
+    n = 35
+    sig = [0.1 + 0.02 * j for j in range(n)]
+    xs = [gaussian_source(g.volume // 2, 300 + j) for j in range(n)]
+    bs = [oracle.apply_A(g, s, x) for s, x in zip(sig, xs)]
+    bd, xd = [dev(b) for b in bs], [dev(x) for x in xs]
+    loss, grad = net.loss_grad([G] * n, sig, bd, xd)
+    one = [net.loss_grad([G], [s], [b], [x]) for s, b, x in zip(sig, bd, xd)]
+    assert abs(loss - np.mean([o[0] for o in one])) <= 1e-12 * loss
+    assert rel_l2(grad, np.mean([o[1] for o in one], axis=0)) <= 1e-5
+    for j in (0, 31, 32, 34):
+        bad = list(bd)
+        bad[j] = -bd[j]
+        with pytest.raises(ks.KSError) as e:
+            net.loss_grad([G] * n, sig, bad, xd)
+        assert e.value.code == -1 and "pair %d" % j in str(e.value)
+    again, _ = net.loss_grad([G] * n, sig, bd, xd)
+    assert again == loss
