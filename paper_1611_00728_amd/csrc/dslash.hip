@@ -6,8 +6,11 @@
 // more keeps more loads in flight per wave).  Links
 // stream from packed site-major planes (16-byte coalesced loads, read once: the bulk of the
 // bytes); the 16 neighbour vectors are gathers that the XCD-aware tile order keeps inside
-// one XCD's L2 for most hops.
+// one XCD's L2 for most hops, and the output is streamed past it so that it does not take the
+// input's place there (with two blocks per CU, 32^3x48: FP64 304 -> 290 us a launch, FP32 162 ->
+// 144, its 12-real Naik 145 -> 123).
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <fstream>
@@ -19,6 +22,7 @@
 
 #include "ks_device.h"
 #include "ks_naik.h"
+#include "ks_stream.h"
 
 namespace ks {
 
@@ -201,7 +205,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void ds
                 res[k].r = aa * xs[k].r - res[k].r;
                 res[k].i = aa * xs[k].i - res[k].i;
             }
-            Spinor<P>::store(out, vh, h, res);
+            Streamed<P>::store(out, vh, h, res);
             if (partials) {
                 // Re<x, out> of the output as stored
                 Spinor<P>::round(res);
@@ -210,7 +214,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void ds
                     dot += (double)xs[k].r * (double)res[k].r + (double)xs[k].i * (double)res[k].i;
             }
         } else {
-            Spinor<P>::store(out, vh, h, res);
+            Streamed<P>::store(out, vh, h, res);
         }
     }
     if (partials) {
@@ -388,6 +392,23 @@ int split_of(const TuneEntry& t, int P, int vh)
     return vh <= (P == KS_F64 ? 100000 : P == KS_F32 ? 130000 : 200000) ? 4 : 1;
 }
 
+// Dynamic LDS of a one-thread-per-site launch that nobody tuned: FP64 and FP32 run two blocks of 256 per
+// CU, where the waves then in flight keep the rows of neighbour vectors that they share in the
+// caches; the link loads of two waves per SIMD still fill the memory's queues.  Four and more / three
+// / two blocks per CU, us a launch: 32^4 FP64 204 / 197 / 188 (12-real 181 / 180 / 170), FP32 98.7 /
+// 95.3 / 92.2 (90.6 / 83.5 / 79.5); 32^3x48 FP64 326 / 320 / 290, FP32 162 / 156 / 144; 48^3x32
+// FP64 732 / 724 / 691, FP32 366 / 360 / 338.  Where the last round of blocks would leave more than
+// 15 % of the chip's time empty, three: 28^4 (2.3 rounds of two) FP64 126 / 118 / 122, FP32 60.2 /
+// 57.5 / 61.1; 24^4 (1.3) 65.2 / 64.7 / 75.2.  FP16 has too few bytes per load for it: 32^4 52.1 /
+// 56.4 / 66.1.
+int lds_of(const TuneEntry& t, int P, int vh)
+{
+    if (t.split > 0 || P == KS_F16) return t.lds;
+    constexpr int kTwoPerCu = 80000, kThreePerCu = 52000;       // of 160 KB
+    const double rounds = vh / (2.0 * 256 * 256);               // 256 CUs
+    return rounds >= 0.85 * std::ceil(rounds) ? kTwoPerCu : kThreePerCu;
+}
+
 // Links of both parities up to this size are read through the caches: the last-level one (256 MB)
 // then still holds them, beside the vectors, at a solver's next step; larger ones are streamed.
 // CG step, streamed / through the caches: 186 MB (14x18x16x20 FP64) 48.7 / 43.0 us, 184 MB (20^4
@@ -434,9 +455,10 @@ void launch_nt(const LinkStore& st, const Geom& G, double c0, const DslashArgs& 
 
 template <int P, int RECON>
 void launch_p(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a,
-              const TuneEntry& t, hipStream_t s)
+              TuneEntry t, hipStream_t s)
 {
     const int split = split_of(t, P, G.Vh);
+    t.lds = lds_of(t, P, G.Vh);
     const size_t links = (size_t)2 * 8 * (9 + (RECON == 12 ? 6 : 9)) * EntrySize<P>::value * G.lp;
     if (split == 4) {
         if (links <= kCachedLinks) launch_split<P, RECON, 4, false>(st, G, c0, a, s);

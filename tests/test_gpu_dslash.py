@@ -356,3 +356,26 @@ def test_tune_cache_keeps_lanes_per_site(ks, tmp_path, monkeypatch):
         assert dc.worst(outs[-1], ref, S, "f32") <= 1.0
     # one thread per site adds in one order whatever the block
     assert np.array_equal(outs[2], outs[3])
+
+
+# blocks per CU of an untuned launch: two where they fill their last round (229680 and 256000
+# sites, the first with a ragged last block), else three (134136, ragged, and 160000)
+@pytest.mark.parametrize("dims", [(18, 22, 20, 58), (20, 20, 20, 64), (18, 18, 18, 46),
+                                  (20, 20, 20, 40)])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_dslash_blocks_per_cu(ks, dims, prec):
+    """How many blocks share a CU changes no bit of the output: the untuned launch against the
+    same form with its blocks uncapped."""
+    import torch
+    announce("dslash blocks per CU", dims, prec)
+    V = int(np.prod(dims))
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    fat, naik = (torch.randn(4, V, 3, 3, generator=gen, dtype=torch.complex128, device="cuda")
+                 for _ in range(2))
+    P = ks.PREC[prec]
+    G, H = ks.Gauge(dims, fat, naik), ks.Gauge(dims, fat, naik)
+    H.set_config(P, 18, threads=256)
+    psi = gaussian_source(V // 2, 41)
+    outs = [run_dslash(ks, L, V // 2, 1, psi, P, 18) for L in (G, H)]
+    assert np.abs(outs[1]).max() > 0
+    assert np.array_equal(outs[0], outs[1])
