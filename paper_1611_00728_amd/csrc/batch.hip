@@ -10,6 +10,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "ks_batch.h"
@@ -22,88 +23,71 @@ namespace {
 constexpr int kFin = 256;
 
 // ---------------------------------------------------------------- multi-RHS vectors
-// Lattice l's part of a vector arena: [3 colours][Vh_l][R] complex, starting at site offset
-// vec_off_l (sum of the Vh of the lattices before it).  The R complex numbers of one site and
-// colour are contiguous, so a lane loads them with 16-byte vector loads.
-
+// Lattice l's part of a vector arena starts at site offset vec_off_l (the sum of the Vh of the
+// lattices before it) and is cut into planes of Vh_l sites with 16 bytes each (8 with one FP32
+// right-hand side), so that a wave's access to a plane is one run of memory:
+//   FP64: [3 colours][R] complex; FP32: [3][R / 2] pairs of complex (the right-hand sides r, r + 1);
+//   binary16: [R] records {FP32 scale n, 3 x half2}, value = n * half (n = the largest real of the
+//   record, as a single-RHS binary16 field stores a site).
+// (With the R entries of a site adjacent instead, a lane's loads of a site lie 16 R bytes apart
+// from its neighbour's and touch R times the cache lines per instruction.)
 template <int P, int R>
 struct MVec {
     using T = typename St<P>::R;
-    static constexpr int CS = P == KS_F64 ? 16 : 8;   // bytes of one complex
-    __device__ static __forceinline__ size_t off(size_t vec_off, int vh, int k, int h)
+    static constexpr int kPer = P == KS_F64 || R == 1 ? 1 : 2;        // complex per plane entry
+    static constexpr int kPlanes = 3 * R / kPer;
+    using E = std::conditional_t<P == KS_F64, double2, std::conditional_t<R == 1, float2, float4>>;
+    template <class B>
+    __device__ static __forceinline__ auto at(B* base, size_t vec_off, int h)
     {
-        return ((vec_off * 3 + (size_t)k * vh + h) * R) * CS;
+        using Q = std::conditional_t<std::is_const_v<B>, const E, E>;
+        return reinterpret_cast<Q*>(base) + vec_off * kPlanes + h;
     }
     __device__ static __forceinline__ void load(const char* base, size_t vec_off, int vh, int h,
                                                 cx<T> v[3][R])
     {
+        const E* p = at(base, vec_off, h);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const char* p = base + off(vec_off, vh, k, h);
-            if constexpr (P == KS_F64) {
+        for (int k = 0; k < 3; ++k)
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const double2 t = reinterpret_cast<const double2*>(p)[r];
-                    v[k][r] = {t.x, t.y};
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; r += 2) {
-                    if (r + 1 < R) {
-                        const float4 t = reinterpret_cast<const float4*>(p)[r / 2];
-                        v[k][r] = {t.x, t.y};
-                        v[k][r + 1] = {t.z, t.w};
-                    } else {
-                        const float2 t = reinterpret_cast<const float2*>(p)[r];
-                        v[k][r] = {t.x, t.y};
-                    }
-                }
+            for (int r = 0; r < R; r += kPer) {
+                const E t = p[(size_t)(k * (R / kPer) + r / kPer) * vh];
+                v[k][r] = {t.x, t.y};
+                if constexpr (kPer == 2) v[k][r + 1] = {t.z, t.w};
             }
-        }
     }
     // v as it reads back after a store (no rounding at FP32 and FP64)
     __device__ static __forceinline__ void round(cx<T>[3][R]) {}
     __device__ static __forceinline__ void store(char* base, size_t vec_off, int vh, int h,
                                                  const cx<T> v[3][R])
     {
+        E* p = at(base, vec_off, h);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            char* p = base + off(vec_off, vh, k, h);
-            if constexpr (P == KS_F64) {
+        for (int k = 0; k < 3; ++k)
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    reinterpret_cast<double2*>(p)[r] = make_double2(v[k][r].r, v[k][r].i);
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; r += 2) {
-                    if (r + 1 < R)
-                        reinterpret_cast<float4*>(p)[r / 2] =
-                            make_float4(v[k][r].r, v[k][r].i, v[k][r + 1].r, v[k][r + 1].i);
-                    else
-                        reinterpret_cast<float2*>(p)[r] = make_float2(v[k][r].r, v[k][r].i);
+            for (int r = 0; r < R; r += kPer) {
+                E t;
+                t.x = v[k][r].r;
+                t.y = v[k][r].i;
+                if constexpr (kPer == 2) {
+                    t.z = v[k][r + 1].r;
+                    t.w = v[k][r + 1].i;
                 }
+                p[(size_t)(k * (R / kPer) + r / kPer) * vh] = t;
             }
-        }
     }
 };
 
-// binary16 inner vectors: one 16-byte record per (site, RHS), {FP32 scale n, 3 x half2}, value
-// = n * half (n = the largest real of the record, as a single-RHS binary16 field stores a site),
-// the R records of a site adjacent: [Vh_l][R] from record offset vec_off_l * R.
 template <int R>
 struct MVec<KS_F16, R> {
     using T = float;
-    __device__ static __forceinline__ const uint4* rec(const char* base, size_t vec_off, int h)
-    {
-        return reinterpret_cast<const uint4*>(base) + (vec_off + (size_t)h) * R;
-    }
     __device__ static __forceinline__ void load(const char* base, size_t vec_off, int vh, int h,
                                                 cx<T> v[3][R])
     {
-        const uint4* p = rec(base, vec_off, h);
+        const uint4* p = reinterpret_cast<const uint4*>(base) + vec_off * R + h;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const uint4 q = p[r];
+            const uint4 q = p[(size_t)r * vh];
             const float n = __uint_as_float(q.x);
             const float2 a = unpack_half2(q.y), b = unpack_half2(q.z), c = unpack_half2(q.w);
             v[0][r] = {n * a.x, n * a.y};
@@ -114,7 +98,7 @@ struct MVec<KS_F16, R> {
     __device__ static __forceinline__ void store(char* base, size_t vec_off, int vh, int h,
                                                  const cx<T> v[3][R])
     {
-        uint4* p = const_cast<uint4*>(rec(base, vec_off, h));
+        uint4* p = reinterpret_cast<uint4*>(base) + vec_off * R + h;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             float n = 0.f;
@@ -129,7 +113,7 @@ struct MVec<KS_F16, R> {
             } else {
                 q.y = q.z = q.w = 0u;
             }
-            p[r] = q;
+            p[(size_t)r * vh] = q;
         }
     }
     // v replaced by the values its records decode to
@@ -163,8 +147,63 @@ __device__ __forceinline__ int lattice_mode(const BatchPair* pairs, int p0, int 
     return ru ? 2 : (busy ? 1 : 0);
 }
 
+// Binary16 hops of hop_site: the products of two halves are added up in FP32 by mixed-precision
+// FMAs straight from the stored words (no conversion instruction, and 25 registers a hop instead
+// of 42 while its loads are in flight), the record's FP32 scale times the store's enters once per
+// colour.  Two hops in flight per wave at three waves per SIMD: one hop 127 us a launch, two 122,
+// four 125 (32^3x48, R = 4; converted at once and scaled entry by entry: 125).
+template <int R>
+__device__ __forceinline__ void hop_site_f16(const LatDesc& L, int h, const int nb[16],
+                                             const void* fat, const void* naik, const char* in,
+                                             cx<float> res[3][R])
+{
+    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+    const int vh = L.g.Vh, lp = L.g.lp;
+    constexpr int kHops = 2;
+    const uvec4* rec = reinterpret_cast<const uvec4*>(in) + L.vec_off * R;
+#pragma unroll 1
+    for (int s0 = 0; s0 < 16; s0 += kHops) {
+        unsigned m[kHops][9];
+        uvec4 v[kHops][R];
+#pragma unroll
+        for (int u = 0; u < kHops; ++u) {
+            load_link_words(s0 < 8 ? fat : naik, (s0 + u) & 7, lp, h, m[u]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[u][r] = rec[(size_t)r * vh + nb[s0 + u]];
+        }
+        // every load of the hops is issued before the first of their values is used
+#pragma unroll
+        for (int u = 0; u < kHops; ++u) {
+#pragma unroll
+            for (int e = 0; e < 9; ++e) asm volatile("" : "+v"(m[u][e]));
+#pragma unroll
+            for (int r = 0; r < R; ++r) asm volatile("" : "+v"(v[u][r]));
+        }
+        const float sc = s0 < 8 ? L.fat_scale : L.naik_scale;
+#pragma unroll
+        for (int u = 0; u < kHops; ++u)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const unsigned w[3] = {v[u][r].y, v[u][r].z, v[u][r].w};
+                const float n = sc * __uint_as_float(v[u][r].x);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    cx<float> t = {0.f, 0.f};
+#pragma unroll
+                    for (int b = 0; b < 3; ++b) {
+                        const half2v x = __builtin_bit_cast(half2v, m[u][a * 3 + b]);
+                        const half2v y = __builtin_bit_cast(half2v, w[b]);
+                        cfma(t, {(float)x.x, (float)x.y}, {(float)y.x, (float)y.y});
+                    }
+                    res[a][r].r = fmaf(n, t.r, res[a][r].r);
+                    res[a][r].i = fmaf(n, t.i, res[a][r].i);
+                }
+            }
+    }
+}
+
 // res_r = (D in_r)(h) for the R right-hand sides of site h, links and vectors of precision PP.
-// UNROLL hops per pass of the 16: FP32 keeps four link and neighbour loads in flight
+// Hops per pass of the 16: FP32 keeps four link and neighbour loads in flight
 // (measured best; a full unroll is slower); FP64 at four hops would spill.
 template <int PP, int R>
 __device__ __forceinline__ void hop_site(const LatDesc& L, int par, int h, const void* fat,
@@ -190,17 +229,16 @@ __device__ __forceinline__ void hop_site(const LatDesc& L, int par, int h, const
     for (int k = 0; k < 3; ++k)
 #pragma unroll
         for (int r = 0; r < R; ++r) res[k][r] = {0, 0};
+    if constexpr (PP == KS_F16) {
+        hop_site_f16<R>(L, h, nb, fat, naik, in, res);
+        return;
+    }
     constexpr int kHopUnroll = PP == KS_F64 ? 1 : 4;
 #pragma unroll kHopUnroll
     for (int s = 0; s < 16; ++s) {
         cx<T> m[9];
         if (s < 8) load_link<PP, 9>(fat, s, g.lp, h, m);
         else load_link<PP, 9>(naik, s - 8, g.lp, h, m);
-        if constexpr (PP == KS_F16) {   // binary16 stores hold link / scale
-            const float sc = s < 8 ? L.fat_scale : L.naik_scale;
-#pragma unroll
-            for (int e = 0; e < 9; ++e) m[e] = {sc * m[e].r, sc * m[e].i};
-        }
         cx<T> v[3][R];
         V::load(in, L.vec_off, vh, nb[s], v);
 #pragma unroll
@@ -723,7 +761,7 @@ __global__ void batch_io_kernel(const LatDesc* __restrict__ lats, char* __restri
     for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < vh; h += gridDim.x * blockDim.x) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            double2* a = reinterpret_cast<double2*>(arena) + ((L.vec_off * 3 + (size_t)k * vh + h) * R + r);
+            double2* a = MVec<KS_F64, R>::at(arena, L.vec_off, h) + (size_t)(k * R + r) * vh;
             if (to_arena) *a = u[(size_t)h * 3 + k];
             else u[(size_t)h * 3 + k] = *a;
         }
@@ -899,13 +937,34 @@ static void batch_setup(BatchCtx* c, hipStream_t s)
         vec_off += (size_t)g->geom.Vh;
     }
     c->total_vh = vec_off;
-    // tile tables for 64, 128 and 256 sites per tile
+    // tile tables for 64, 128 and 256 sites per tile.  Blocks go round robin to the eight XCDs, and
+    // the vectors of R right-hand sides are most of what an L2 could hold between their reads by
+    // neighbouring sites: each XCD gets an eighth of every lattice (so that it keeps work while
+    // any lattice iterates), in columns of kColumn z-planes walked along t.  32^3x48, binary16,
+    // R = 4: the hopping term's two launches 122 + 130 us in index order, 131 + 131 with eighths alone,
+    // 121 + 127 / 120 + 126 / 119 + 126 / 119 + 126 / 126 + 127 with columns of 1 / 2 / 4 / 8 / 16
+    // planes; update and direction, which meet their tiles in the same L2: 66 + 36.5 to 64 + 35.6.
+    constexpr int kColumn = 4;
     size_t max_tiles = 0;
     for (int k = 0; k < 3; ++k) {
         std::vector<int2> tt;
         for (int l = 0; l < nlat; ++l) {
             if (k == 0) lats[l].tile_begin = (int)tt.size();
-            for (int h0 = 0; h0 < lats[l].g.Vh; h0 += kTileSizes[k]) tt.push_back(make_int2(l, h0));
+            const Geom& g = lats[l].g;
+            std::vector<int> seq;
+            for (int h0 = 0; h0 < g.Vh; h0 += kTileSizes[k]) seq.push_back(h0);
+            const int plane = g.n[0] / 2 * g.n[1];
+            auto walk = [&](int h0) {
+                const int z = h0 / plane % g.n[2], t = h0 / plane / g.n[2];
+                return std::make_pair(z / kColumn * g.n[3] + t, h0);
+            };
+            std::sort(seq.begin(), seq.end(), [&](int a, int b) { return walk(a) < walk(b); });
+            const size_t t0 = tt.size();
+            tt.resize(t0 + seq.size());
+            size_t at = 0;
+            for (size_t xcd = 0; xcd < 8; ++xcd)
+                for (size_t t = t0; t < tt.size(); ++t)
+                    if ((t & 7) == xcd) tt[t] = make_int2(l, seq[at++]);
         }
         c->ntiles[k] = (int)tt.size();
         c->tiles[k] = static_cast<int2*>(device_alloc(sizeof(int2) * tt.size()));

@@ -108,11 +108,14 @@ struct LinkPack {
     }
 };
 
+// Links are in global memory, which the compiler cannot know of a pointer that a kernel read from
+// memory itself (a batch's lattices): its flat loads count as LDS accesses too.
 template <bool kStream, class T>
 __device__ __forceinline__ T link_read(const T* p)
 {
-    if constexpr (kStream) return __builtin_nontemporal_load(p);
-    else return *p;
+    const auto* g = (const __attribute__((address_space(1))) T*)p;
+    if constexpr (kStream) return __builtin_nontemporal_load(g);
+    else return *g;
 }
 
 // the N entries of link `slot` at site h from planes of lp sites.  kStream: read past the caches
@@ -158,6 +161,21 @@ __device__ __forceinline__ void load_link(const void* base, int slot, int lp, in
             static_assert(P == KS_F16 && LP::NR <= 2, "unsupported link packing");
         }
     }
+}
+
+// the nine binary16 entries of an 18-real link as stored (real half low, imaginary half high)
+__device__ __forceinline__ void load_link_words(const void* base, int slot, int lp, int h,
+                                                unsigned m[9])
+{
+    const char* sb = static_cast<const char*>(base) + (size_t)slot * 36 * lp;
+    const uvec4 a = link_read<true>(reinterpret_cast<const uvec4*>(sb) + h);
+    const uvec4 b = link_read<true>(reinterpret_cast<const uvec4*>(sb + (size_t)16 * lp) + h);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        m[e] = a[e];
+        m[4 + e] = b[e];
+    }
+    m[8] = link_read<true>(reinterpret_cast<const unsigned*>(sb + (size_t)32 * lp) + h);
 }
 
 // ---------------------------------------------------------------- colour vectors

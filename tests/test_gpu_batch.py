@@ -164,3 +164,19 @@ def test_batch_zero_rhs_and_max_iter(ks, fields, inner):
         tr = true_rel(gs[0], 4 * masses[0] ** 2, b, host(xs[k]))
         assert 1e-6 < tr < 1.0 and abs(st[k]["true_rel_resid"] - tr) <= 1e-6 * tr
     B.free()
+
+
+# tiles that straddle planes, end ragged and fall in columns of unequal depth (10 = 4 + 4 + 2 planes)
+@pytest.mark.parametrize("dims", [(6, 4, 10, 6), (16, 8, 6, 4), (8, 8, 10, 12)])
+@pytest.mark.parametrize("nrhs,inner", [(4, "f16"), (4, "f32"), (2, "f16"), (1, "f32"), (4, "f64")])
+def test_batch_tile_order(ks, dims, nrhs, inner):
+    announce("batch tile order", dims, nrhs, inner)
+    gs = [make_gauge(d, 0.4, 4500) for d in (dims, (4, 4, 4, 4))]
+    masses = np.array([0.3, 0.25])
+    B = ks.Batch([g.dims for g in gs], [g.fat for g in gs], [g.naik for g in gs], nrhs,
+                 ks.PREC[inner])
+    rc, st, bh, xh = run_batch(ks, B, gs, masses, nrhs, check_every=4)
+    assert rc == 0, st
+    for p, (b, x) in enumerate(zip(bh, xh)):
+        assert true_rel(gs[p // nrhs], 4 * masses[p // nrhs] ** 2, b, x) <= 1e-10
+    B.free()
