@@ -772,7 +772,12 @@ __global__ void batch_io_kernel(const LatDesc* __restrict__ lats, char* __restri
 
 // ---------------------------------------------------------------- launchers
 
-constexpr int kUpdateGrid = 2048;   // blocks of the update and direction kernels
+// Threads of the update and direction kernels' grids, which stride over the tiles: all that the chip
+// holds at two waves per SIMD.  Every block sums its lattices' partials once per lattice it meets, so
+// fewer blocks than tiles pay on one large lattice (3072 tiles of 256, binary16, R = 4: 62 + 36 us
+// against 66 + 39 with a block per tile), while a batch whose tiles all fit takes a block per tile
+// (3212 tiles of 64, FP32, R = 4: 23.1 + 14.3 us, 24.5 + 16.7 with 2048 blocks).
+constexpr int kUpdateThreads = 2048 * 256;
 
 template <int R, int NT>
 struct BatchLaunch {
@@ -808,7 +813,7 @@ struct BatchLaunch {
         hop(c, true, s);
         // the update kernels stride over the tiles with a capped grid: every block sums its
         // lattices' partials, once per lattice it meets
-        const int ug = std::min(nt, kUpdateGrid);
+        const int ug = std::min(nt, kUpdateThreads / NT);
         if (c.prec == KS_F64) {
             batch_update_kernel<KS_F64, R, NT><<<ug, NT, 0, s>>>(c.lats_dev, tl, nt, c.x64, c.ps,
                                                                  c.qs, c.rs, c.r64, c.pairs,
