@@ -6,7 +6,7 @@
 // changes S by sum_{x,mu} 2 Re Tr[dV_mu(x) FV_mu(x) + dW_mu(x) FW_mu(x)] with
 //     FV_mu(x) = eps(x) sum_i r_i Psi_i(x+mu) Psi_i(x)^+,
 //     FW_mu(x) = eps(x) sum_i r_i Psi_i(x+3mu) Psi_i(x)^+,      eps = +1 even, -1 odd sites.
-// The Y_i come from a multi-vector FP64 hopping term (links read once for up to five X_i);
+// The Y_i come from a multi-vector FP64 hopping term (links read once for up to ten X_i);
 // one pass over (direction, site) pairs then builds both outer-product sums in registers and
 // writes them in the canonical link layout.
 #include <algorithm>
@@ -21,69 +21,94 @@ namespace ks {
 namespace {
 
 constexpr int kMaxTerms = 32;
+constexpr int kTile = 64;               // sites
 
-struct Terms {
-    const double2* psi[2][kMaxTerms];   // [parity][term]: FP64 planes [3][Vh]
-    double r[kMaxTerms];
+// The n vectors of one parity: [tiles of 64 sites][n terms][3 colours][64] complex, so that all that
+// a neighbourhood of sites holds is one run of memory.  (As 3 n planes of Vh sites each, at a pitch
+// that is a multiple of the caches' way size, the rows of a neighbourhood fell on the same sets.)
+struct TermVecs {
+    double2* p;
     int n;
+    __device__ __forceinline__ double2* at(int h) const
+    {
+        return p + (size_t)(h / kTile) * (n * 3 * kTile) + h % kTile;
+    }
 };
 
-__device__ __forceinline__ void load_psi(const double2* p, int vh, int h, cx<double> v[3])
+__device__ __forceinline__ void load_psi(const double2* site, int term, cx<double> v[3])
 {
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const double2 t = p[(size_t)k * vh + h];
+        const double2 t = site[(term * 3 + k) * kTile];
         v[k] = {t.x, t.y};
     }
 }
 
-// y_k = D_{par} x_k for K vectors at once (FP64, 18-real, 8-way links of the output parity):
-// each of a site's 16 link matrices is loaded once and applied to the K vectors, so the
-// links' bytes are read once per K outputs instead of once per output.
-constexpr int kMultiMax = 5;   // nine terms in two passes (measured: 5 beats 3 and 4 per pass)
-
-struct MultiVec {
-    const double2* in[kMultiMax];
-    double2* out[kMultiMax];
+struct TermPtrs {
+    const double2* x[kMaxTerms];
+    double r[kMaxTerms];
 };
 
-// Two lanes per output site: lane 0 of the pair takes the eight one-link matrices, lane 1 the
-// eight Naik matrices (twice the waves, half of each lane's chain of dependent loads); one
-// shuffle adds the halves and lane 0 stores.
-template <int K>
-__global__ __launch_bounds__(kBlock) void dslash_multi_kernel(Geom g, int par,
-                                                              const void* __restrict__ fat,
-                                                              const void* __restrict__ naik,
-                                                              MultiVec mv, float fat_scale,
-                                                              float naik_scale)
+// caller's vectors [Vh][3], one per blockIdx.y
+__global__ __launch_bounds__(kBlock) void force_import_kernel(int vh, TermPtrs t, TermVecs x)
+{
+    const int h = blockIdx.x * kBlock + threadIdx.x;
+    if (h >= vh) return;
+    const double2* src = t.x[blockIdx.y] + (size_t)3 * h;
+    double2* dst = x.at(h) + blockIdx.y * (3 * kTile);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) dst[k * kTile] = src[k];
+}
+
+// y_k = D_{par} x_k for the terms [first, last) at once (FP64, 18-real, 8-way links of the output
+// parity): each of a site's 16 link matrices is read once for all of them.  Two lanes per output
+// site, the halves of a wave: with one group of K terms a half takes the one-link or the Naik
+// matrices and a shuffle adds them; with two groups a half takes K terms, which serves up to ten
+// with the accumulators of five, the second half's link loads being hits of the same instruction.
+// Bound by the vectors that the gathers bring to L2 again and again: two blocks per CU (dynamic
+// LDS, and registers for all loads of a hop) keep the span of sites in flight short.  Nine terms,
+// 32^3x48: 1010 us in passes of five and four from planes of Vh sites; 780 in one.  Links through the
+// caches 850, three blocks per CU 860, four lanes per site by hops 800-910, four groups of three
+// terms 860-1010.  Ten terms 1875 us for the whole force, 2230 in two passes of five.
+constexpr int kSites = 32;              // per wave
+constexpr int kMultiMax = 10;           // terms per pass
+constexpr int kMultiLds = 80000;        // of a CU's 160 KB
+
+template <int K, int kGroups>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+dslash_multi_kernel(Geom g, int par, const void* __restrict__ fat, const void* __restrict__ naik,
+                    TermVecs in, TermVecs out, int first, int last, float fat_scale,
+                    float naik_scale)
 {
     const int vh = g.Vh;
-    const int t = xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    const int h = t >> 1;
-    const int kind = t & 1;                 // 0: one-link, 1: Naik
-    const bool live = h < vh;
-    const int hs = live ? h : vh - 1;       // a dead lane shadows a live site (no store)
+    const int wave = xcd_tile(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
+    const int hh = wave * kSites + threadIdx.x % kSites;
+    const int part = (threadIdx.x & 63) / kSites;
+    const int t0 = first + (kGroups == 2 ? part * K : 0);
+    const int s0 = kGroups == 2 ? 0 : part * 8;
+    const bool live = hh < vh;
+    const int h = live ? hh : vh - 1;       // a dead lane shadows a live site (no store)
     int c[4];
-    cb_coords(g, hs, par, c);
+    cb_coords(g, h, par, c);
     const int i = site_index(g, c);
     cx<double> res[K][3];
 #pragma unroll
     for (int q = 0; q < K; ++q)
 #pragma unroll
         for (int a = 0; a < 3; ++a) res[q][a] = {0.0, 0.0};
-    const void* links = kind ? naik : fat;
-    const double sc = kind ? (double)naik_scale : (double)fat_scale;
 #pragma unroll 1
-    for (int s = 0; s < 8; ++s) {
-        // slots 0-3: +mu, 4-7: -mu; backward slots hold the negated adjoint of the link
-        const int dist = (s & 4) ? (kind ? -3 : -1) : (kind ? 3 : 1);
-        const int nb = hop_cb(g, i, c, s & 3, dist);
+    for (int u = 0; u < 8 * kGroups; ++u) {
+        const int s = s0 + u;
+        // slots 0-3: +mu, 4-7: -mu, 8-15: the Naik ones; backward slots hold the negated adjoint
+        const int nb = hop_cb(g, i, c, s & 3, (s & 8 ? 3 : 1) * (s & 4 ? -1 : 1));
+        const double sc = s & 8 ? (double)naik_scale : (double)fat_scale;
         cx<double> m[9];
-        load_link<KS_F64, 9>(links, s, g.lp, hs, m);
+        load_link<KS_F64, 9>(s & 8 ? naik : fat, s & 7, g.lp, h, m);
+        const double2* site = in.at(nb);
 #pragma unroll
         for (int q = 0; q < K; ++q) {
             cx<double> v[3];
-            load_psi(mv.in[q], vh, nb, v);
+            load_psi(site, min(t0 + q, last - 1), v);
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 cx<double> u = {0.0, 0.0};
@@ -94,58 +119,63 @@ __global__ __launch_bounds__(kBlock) void dslash_multi_kernel(Geom g, int par,
             }
         }
     }
+    if constexpr (kGroups == 1) {
 #pragma unroll
-    for (int q = 0; q < K; ++q)
+        for (int q = 0; q < K; ++q)
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            res[q][a].r += __shfl_xor(res[q][a].r, 1, 64);
-            res[q][a].i += __shfl_xor(res[q][a].i, 1, 64);
-        }
-    if (!live || kind) return;
+            for (int a = 0; a < 3; ++a) {
+                res[q][a].r += __shfl_xor(res[q][a].r, 32, 64);
+                res[q][a].i += __shfl_xor(res[q][a].i, 32, 64);
+            }
+    }
+    if (!live || (kGroups == 1 && part)) return;
+    double2* o = out.at(h);
 #pragma unroll
-    for (int q = 0; q < K; ++q)
+    for (int q = 0; q < K; ++q) {
+        if (t0 + q >= last) break;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) mv.out[q][(size_t)a * vh + h] = make_double2(res[q][a].r, res[q][a].i);
+        for (int a = 0; a < 3; ++a)
+            o[((t0 + q) * 3 + a) * kTile] = make_double2(res[q][a].r, res[q][a].i);
+    }
 }
 
-template <int K>
-void launch_multi_k(int k, unsigned nb, const Geom& G, const LinkStore& st, const MultiVec& mv,
-                    hipStream_t s)
+template <int K, int kGroups>
+void launch_multi_k(const Geom& G, const LinkStore& st, TermVecs in, TermVecs out, int first,
+                    int last, hipStream_t s)
 {
     if constexpr (K > 1) {
-        if (k < K) {
-            launch_multi_k<K - 1>(k, nb, G, st, mv, s);
+        if (last - first <= kGroups * (K - 1)) {
+            launch_multi_k<K - 1, kGroups>(G, st, in, out, first, last, s);
             return;
         }
     }
-    dslash_multi_kernel<K><<<nb, kBlock, 0, s>>>(G, 1, st.fat[1], st.naik[1], mv, st.fat_scale,
-                                                st.naik_scale);
-}
-
-void launch_multi(int k, unsigned nb, const Geom& G, const LinkStore& st, const MultiVec& mv,
-                  hipStream_t s)
-{
-    launch_multi_k<kMultiMax>(k, nb, G, st, mv, s);
+    dslash_multi_kernel<K, kGroups><<<blocks_for(2L * G.Vh), kBlock, kMultiLds, s>>>(
+        G, 1, st.fat[1], st.naik[1], in, out, first, last, st.fat_scale, st.naik_scale);
+    KS_HIP(hipGetLastError());
 }
 
 // One block: kOuterSites consecutive lexicographic sites x the four directions (wave w takes
 // mu = w), so the four waves that read a site's vectors share them through one CU's L1; blocks
 // are remapped so that each XCD walks one contiguous range of sites.  Thread (mu, x) writes
-// link t = mu V + x.
+// link t = mu V + x.  The lower half of a wave takes the even sites of the block's pairs of x
+// neighbours, the upper half the odd ones, so that each half reads one run of memory (sites in x
+// order alternate between the two parities' fields, which doubles the cache accesses: 32^3x48, nine
+// terms, 1016 -> 860 us).  The next term's loads ahead of this one's products: no gain (156
+// registers, three waves per SIMD).
 constexpr int kOuterSites = 64;
 
-__global__ __launch_bounds__(4 * kOuterSites) void force_outer_kernel(Geom g, Terms terms,
-                                                                      double2* __restrict__ fv,
-                                                                      double2* __restrict__ fw)
+__global__ __launch_bounds__(4 * kOuterSites) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+force_outer_kernel(Geom g, TermPtrs terms, TermVecs even, TermVecs odd, double2* __restrict__ fv,
+                   double2* __restrict__ fw)
 {
     const int mu = threadIdx.x / kOuterSites;
     const int lane = threadIdx.x % kOuterSites;
     const long x0 = (long)xcd_tile(blockIdx.x, gridDim.x) * kOuterSites;
     const bool full = x0 + kOuterSites <= g.V;   // uniform over the block
-    const long xl = x0 + lane;
-    if (!full && xl >= g.V) return;               // only in a ragged last block
-    const int x = (int)(xl < g.V ? xl : g.V - 1);
-    const long t = (long)mu * g.V + x;
+    const int par = lane >> 5;
+    const long xe = x0 + 2 * (lane & 31);
+    if (!full && xe >= g.V) return;               // only in a ragged last block
+    int x = (int)xe;
     int c[4];
     int r = x;
 #pragma unroll
@@ -154,22 +184,27 @@ __global__ __launch_bounds__(4 * kOuterSites) void force_outer_kernel(Geom g, Te
         r /= g.n[d];
     }
     c[3] = r;
-    const int par = (c[0] + c[1] + c[2] + c[3]) & 1;
+    const int up = (c[0] + c[1] + c[2] + c[3] + par) & 1;   // the pair's site of parity par
+    x += up;
+    c[0] += up;
+    const long t = (long)mu * g.V + x;
     const int h = x >> 1;
     const int n1 = hop_cb(g, x, c, mu, +1);
     const int n3 = hop_cb(g, x, c, mu, +3);
-    const int vh = g.Vh;
     cx<double> a1[9], a3[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) {
         a1[e] = {0.0, 0.0};
         a3[e] = {0.0, 0.0};
     }
-    for (int i = 0; i < terms.n; ++i) {
+    const double2* s0 = (par ? odd : even).at(h);
+    const double2* s1 = (par ? even : odd).at(n1);
+    const double2* s3 = (par ? even : odd).at(n3);
+    for (int i = 0; i < even.n; ++i) {
         cx<double> p0[3], p1[3], p3[3];
-        load_psi(terms.psi[par][i], vh, h, p0);
-        load_psi(terms.psi[1 - par][i], vh, n1, p1);
-        load_psi(terms.psi[1 - par][i], vh, n3, p3);
+        load_psi(s0, i, p0);
+        load_psi(s1, i, p1);
+        load_psi(s3, i, p3);
         const double ri = terms.r[i];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -195,14 +230,14 @@ __global__ __launch_bounds__(4 * kOuterSites) void force_outer_kernel(Geom g, Te
         dvec2* o1 = reinterpret_cast<dvec2*>(fv + ((size_t)mu * g.V + x0) * 9);
         dvec2* o3 = reinterpret_cast<dvec2*>(fw + ((size_t)mu * g.V + x0) * 9);
 #pragma unroll
-        for (int e = 0; e < 9; ++e) sw[lane * 9 + e] = dvec2{eps * a1[e].r, eps * a1[e].i};
+        for (int e = 0; e < 9; ++e) sw[(int)(x - x0) * 9 + e] = dvec2{eps * a1[e].r, eps * a1[e].i};
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 9; ++k)
             __builtin_nontemporal_store(sw[k * kOuterSites + lane], o1 + k * kOuterSites + lane);
         __syncthreads();
 #pragma unroll
-        for (int e = 0; e < 9; ++e) sw[lane * 9 + e] = dvec2{eps * a3[e].r, eps * a3[e].i};
+        for (int e = 0; e < 9; ++e) sw[(int)(x - x0) * 9 + e] = dvec2{eps * a3[e].r, eps * a3[e].i};
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 9; ++k)
@@ -227,35 +262,40 @@ void force_core(ks_gauge_t g, int nterm, const double* residues, const double* c
 {
     Workspace& w = workspace(g);
     const Geom& G = g->geom;
-    const size_t fb = field_bytes(G, KS_F64);
-    while ((int)w.force_psi.size() < 2 * nterm) {
-        w.force_psi.push_back(static_cast<double*>(device_alloc(fb)));
-        w.bytes += fb;
+    if (w.force_terms < nterm) {
+        const size_t ab = (size_t)blocks_for(G.Vh, kTile) * kTile * 3 * sizeof(double2);
+        for (double*& v : w.force_psi) {
+            device_free(v);
+            v = nullptr;
+        }
+        w.bytes -= 2 * ab * w.force_terms;
+        w.force_terms = 0;
+        for (double*& v : w.force_psi) v = static_cast<double*>(device_alloc(ab * nterm));
+        w.force_terms = nterm;
+        w.bytes += 2 * ab * nterm;
     }
-    Terms terms{};
-    terms.n = nterm;
+    const TermVecs even{reinterpret_cast<double2*>(w.force_psi[0]), nterm};
+    const TermVecs odd{reinterpret_cast<double2*>(w.force_psi[1]), nterm};
+    TermPtrs terms{};
     for (int i = 0; i < nterm; ++i) {
-        import_field(G, KS_F64, x_even[i], w.force_psi[2 * i], s);
-        terms.psi[0][i] = reinterpret_cast<const double2*>(w.force_psi[2 * i]);
-        terms.psi[1][i] = reinterpret_cast<const double2*>(w.force_psi[2 * i + 1]);
+        terms.x[i] = reinterpret_cast<const double2*>(x_even[i]);
         terms.r[i] = residues[i];
     }
-    // Y_i = D_oe X_i, up to kMultiMax terms per pass over the odd sites' links
+    force_import_kernel<<<dim3(blocks_for(G.Vh), nterm), kBlock, 0, s>>>(G.Vh, terms, even);
+    KS_HIP(hipGetLastError());
+    // Y_i = D_oe X_i, up to kMultiMax terms per pass over the odd sites' links, in even shares
     const LinkStore& st = g->store[KS_F64][recon_index(KS_RECON_18)];
     if (!st.ready) gauge_prepare(g, KS_F64, KS_RECON_18, s);
-    for (int i0 = 0; i0 < nterm; i0 += kMultiMax) {
-        const int k = std::min(kMultiMax, nterm - i0);
-        MultiVec mv{};
-        for (int q = 0; q < k; ++q) {
-            mv.in[q] = terms.psi[0][i0 + q];
-            mv.out[q] = reinterpret_cast<double2*>(w.force_psi[2 * (i0 + q) + 1]);
-        }
-        const unsigned nb = (unsigned)blocks_for(2L * G.Vh);   // two lanes per site
-        launch_multi(k, nb, G, st, mv, s);
-        KS_HIP(hipGetLastError());
+    const int passes = (nterm + kMultiMax - 1) / kMultiMax;
+    for (int k = 0; k < passes; ++k) {
+        const int a = nterm * k / passes, b = nterm * (k + 1) / passes;
+        // up to five terms the halves of a wave share one group's matrices (five, 32^3x48: 1180 us
+        // for the whole force against 1204 with two groups, where 1.5 times the loads serve six)
+        if (b - a <= kMultiMax / 2) launch_multi_k<kMultiMax / 2, 1>(G, st, even, odd, a, b, s);
+        else launch_multi_k<kMultiMax / 2, 2>(G, st, even, odd, a, b, s);
     }
     force_outer_kernel<<<(unsigned)((G.V + kOuterSites - 1) / kOuterSites), 4 * kOuterSites, 0, s>>>(
-        G, terms, reinterpret_cast<double2*>(force_fat), reinterpret_cast<double2*>(force_naik));
+        G, terms, even, odd, reinterpret_cast<double2*>(force_fat), reinterpret_cast<double2*>(force_naik));
     KS_HIP(hipGetLastError());
 }
 

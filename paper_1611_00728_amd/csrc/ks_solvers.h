@@ -46,8 +46,9 @@ struct Workspace {
     // full-lattice solve, FP64 planes: even right-hand side of the Schur system, even and odd
     // temporaries, and the odd b and x of the boundary call
     double* full[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-    // force: per term the even solution and its odd hopping image, FP64 planes
-    std::vector<double*> force_psi;
+    // force: the even solutions and their odd hopping images, room for force_terms of each
+    double* force_psi[2] = {nullptr, nullptr};
+    int force_terms = 0;
     // multi-shift refinement of several shifts at once: batched CG contexts on this gauge
     // (1, 2 or 4 right-hand sides) and boundary-layout vectors for them
     struct BatchCtx* ms_batch[3] = {nullptr, nullptr, nullptr};

@@ -82,3 +82,26 @@ def test_force_argument_errors(ks):
         ks.force(G, [1.0], [x], fv, fv)
     with pytest.raises(ValueError):
         ks.force(G, [1.0], [x], fv[:10], torch.zeros_like(fv))
+
+
+# one group of terms per pass up to five, two groups (odd counts leave an empty place in the second)
+# up to ten, then two and three passes; 300 = 9 * 32 + 12 sites per parity end ragged
+@pytest.mark.parametrize("dims,nterm", [((4, 4, 4, 4), 5), ((6, 10, 10, 4), 6), ((4, 4, 6, 4), 7),
+                                        ((4, 6, 4, 4), 10), ((10, 6, 10, 4), 11), ((4, 4, 4, 4), 21)])
+def test_force_terms_per_pass(ks, dims, nterm):
+    announce("force terms", dims, nterm)
+    import torch
+    g = make_gauge(dims, 0.5, 96)
+    G = ks.Gauge(dims, g.fat, g.naik)
+    rng = np.random.default_rng(97)
+    xs = [gaussian_source(g.volume // 2, 98 + i) for i in range(nterm)]
+    # fewer terms after more and more after fewer: the vectors' room is kept or grown
+    for n in (nterm, 2, nterm):
+        res = rng.uniform(0.1, 2.0, n)
+        fv = torch.zeros(4 * g.volume * 9, dtype=torch.complex128, device="cuda")
+        fw = torch.zeros_like(fv)
+        ks.force(G, res, [dev(x) for x in xs[:n]], fv, fw)
+        torch.cuda.synchronize()
+        ov, ow = oracle.force_outer(g, res, xs[:n])
+        for got, ref in ((host(fv).reshape(ov.shape), ov), (host(fw).reshape(ow.shape), ow)):
+            assert np.max(np.abs(got - ref)) <= 1e-12 * np.max(np.abs(ref))
