@@ -123,11 +123,26 @@ def _check(rc: int):
         raise KSError(rc, lib().ks_last_error().decode())
 
 
+_current_stream = None
+
+
 def _stream(stream):
+    """The given stream, or torch's current one, whose handle torch's raw accessors give without
+    building a Stream object (8^4 FP64 hopping term and export: 14.9 us a pair of calls, 3.1 of each
+    in the object; 9.8 with the raw handle)."""
+    global _current_stream
     if stream is not None:
         return _vp(int(stream))
-    import torch
-    return _vp(torch.cuda.current_stream().cuda_stream)
+    if _current_stream is None:
+        import torch
+        torch.cuda.current_stream()          # initialises the device, or raises
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        if raw and device:
+            _current_stream = lambda: raw(device())
+        else:
+            _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    return _vp(_current_stream())
 
 
 def _dev_ptr(t, what="tensor"):

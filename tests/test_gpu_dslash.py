@@ -379,3 +379,23 @@ def test_dslash_blocks_per_cu(ks, dims, prec):
     outs = [run_dslash(ks, L, V // 2, 1, psi, P, 18) for L in (G, H)]
     assert np.abs(outs[1]).max() > 0
     assert np.array_equal(outs[0], outs[1])
+
+
+def test_calls_follow_the_current_stream(ks):
+    """Without a stream argument a call goes to torch's current stream, whichever thread and
+    whatever stream was current at an earlier call."""
+    announce("current stream")
+    import threading
+    import torch
+    now = lambda: ks._stream(None).value or 0
+    assert now() == torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert now() == s.cuda_stream != 0
+        seen = []
+        t = threading.Thread(target=lambda: seen.append(now()))   # streams are per thread
+        t.start()
+        t.join()
+        assert seen == [torch.cuda.default_stream().cuda_stream]
+        assert ks._stream(s.cuda_stream).value == s.cuda_stream
+    assert now() == torch.cuda.current_stream().cuda_stream
