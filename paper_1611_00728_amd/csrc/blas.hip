@@ -3,6 +3,7 @@
 #include <algorithm>
 
 #include "ks_blas.h"
+#include "ks_cg_step.h"
 
 namespace ks {
 
@@ -156,42 +157,6 @@ __global__ __launch_bounds__(kBlock) void xpay_kernel(int vh, const void* __rest
 
 // ---------------------------------------------------------------- fused CG step
 
-// Every block reduces the previous kernel's partial sums itself: thread t adds partials t,
-// t + NT, ... then the fixed block order, so all blocks hold the same value bit for bit.
-// fused_load gives a thread's share, fused_total the block's total in every thread (it passes
-// one block barrier).
-template <int NT>
-__device__ __forceinline__ double fused_load(const double* __restrict__ in, int n)
-{
-    double t = 0.0;
-    for (int k = threadIdx.x; k < n; k += NT) t += in[k];
-    return t;
-}
-
-template <int NT>
-__device__ __forceinline__ double fused_total(double t)
-{
-    __shared__ double part[NT / 64];
-    t = wave_sum(t);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = t;
-    __syncthreads();
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < NT / 64; ++k) s += part[k];
-    return s;
-}
-
-// Keeps a vector's loads ahead of what follows: they are in flight together with the partial
-// sums' and the state's, so a step's kernel waits for memory once and not once for each of them
-// (8^4 FP64 with the register sums of wave_sum: update 5.3 -> 3.1 us, direction 4.0 -> 2.9 us a
-// launch).
-template <class R>
-__device__ __forceinline__ void pin(cx<R> v[3])
-{
-#pragma unroll
-    for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(v[k].r), "+v"(v[k].i));
-}
-
 template <int P, int NT>
 __global__ __launch_bounds__(NT) void cg_update_kernel(int vh, void* __restrict__ x,
                                                        const void* __restrict__ p,
@@ -272,9 +237,6 @@ __global__ __launch_bounds__(NT) void cg_update_kernel(int vh, void* __restrict_
     if (threadIdx.x == 0) rr_part[blockIdx.x] = s;
 }
 
-// Decides from the copies the update kernel took (s_*) and from fields no block writes here
-// (stop2, delta, max_iter), so every block takes the same branch; the lead thread alone
-// writes the live state.
 template <int P, int NT>
 __global__ __launch_bounds__(NT) void cg_beta_xpay_kernel(int vh, const void* __restrict__ r,
                                                           void* __restrict__ p,
@@ -285,10 +247,8 @@ __global__ __launch_bounds__(NT) void cg_beta_xpay_kernel(int vh, const void* __
 {
     using R = typename St<P>::R;
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-    const int stop = st->s_gate;
+    const StepEnd end(st);
     const double share = fused_load<NT>(rr_part, nrr);
-    const double s_rho = st->s_rho, maxr = st->s_maxr, stop2 = st->stop2, delta = st->delta;
-    const int iter = st->s_iter + 1, max_iter = st->max_iter;
     const int h = blockIdx.x * NT + threadIdx.x;
     cx<R> rv[3], pv[3];
     if (h < vh) {
@@ -297,40 +257,9 @@ __global__ __launch_bounds__(NT) void cg_beta_xpay_kernel(int vh, const void* __
         pin(rv);
         pin(pv);
     }
-    if (stop) return;
-    const double rho_new = fused_total<NT>(share);
-    if (lead) {
-        st->iter = iter;
-        st->rho_new = rho_new;
-    }
-    if (!isfinite(rho_new)) {
-        if (lead) {
-            st->status = KS_ERR_NONFINITE;
-            st->gate = 1;
-        }
-        return;
-    }
-    const double rn = sqrt(rho_new);
-    if (rho_new <= stop2 || rn < delta * maxr) {
-        // FP64 recomputation of r = b - A x decides (reliable update or final check); the
-        // step's beta is then not a CG coefficient
-        if (lead) {
-            st->ru_pending = 1;
-            st->gate = 1;
-            if (iter - 1 < coef_cap) coef[2 * (iter - 1) + 1] = __builtin_nan("");
-        }
-        return;
-    }
-    const double beta = rho_new / s_rho;
-    const bool last = iter >= max_iter;
-    if (lead) {
-        if (iter - 1 < coef_cap) coef[2 * (iter - 1) + 1] = beta;
-        st->beta = beta;
-        st->rho = rho_new;
-        st->maxr = fmax(maxr, rn);
-        if (last) st->gate = 1;
-    }
-    if (last || h >= vh) return;
+    if (end.stop) return;
+    double beta;
+    if (!end.decide(st, fused_total<NT>(share), lead, coef, coef_cap, beta) || h >= vh) return;
     const R b = (R)beta;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {

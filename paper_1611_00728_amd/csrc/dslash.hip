@@ -20,6 +20,8 @@
 #include <utility>
 #include <vector>
 
+#include "ks_blas.h"
+#include "ks_cg_step.h"
 #include "ks_device.h"
 #include "ks_naik.h"
 #include "ks_stream.h"
@@ -240,12 +242,15 @@ __device__ __forceinline__ R split_sum(R v)
     return v;
 }
 
-template <int P, int RECON, bool XPAY, int S, bool kStream>
+//
+// kDir: the input direction is p = r + beta p of the CG step before (see CGDirection), which saves the
+// launch that would write it; both hopping terms form the same bits from the same values.
+template <int P, int RECON, bool XPAY, int S, bool kStream, bool kDir>
 __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
     Geom g, int par, const void* __restrict__ fat, const void* __restrict__ naik,
     const void* __restrict__ in, void* __restrict__ out, const void* __restrict__ xv, double a,
     double* __restrict__ partials, const int* __restrict__ gate, float fat_scale, float naik_scale,
-    double naik_c0)
+    double naik_c0, CGDirection dir)
 {
     using R = typename St<P>::R;
     static_assert(S == 4 || S == 8, "a lane's slots j + S u lie in one half of the 16 for each u");
@@ -253,7 +258,15 @@ __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
     constexpr int kBlockSites = kSplitThreads / S;
     // the gate's load overlaps the others: a launch that it stops has read links for nothing,
     // one that it lets through does not wait for it first
-    const int stop = gate ? *gate : 0;
+    int stop;
+    double share = 0.0, beta = 0.0;
+    if constexpr (kDir && !XPAY) {
+        stop = dir.st->s_gate;
+        share = fused_load<kSplitThreads>(dir.rr_part, dir.nrr);
+    } else {
+        stop = gate ? *gate : 0;
+        if (kDir) beta = dir.st->beta;
+    }
     const int lane = threadIdx.x & 63;
     const int j = lane / kSites;
     const int vh = g.Vh;
@@ -264,11 +277,18 @@ __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
     int c[4];
     cb_coords(g, h, par, c);
     const int i = site_index(g, c);
-    cx<R> xs[3];
-    if (XPAY) Spinor<P>::load(xv, vh, h, xs);
+    cx<R> xs[3], rs[3];
+    if constexpr (XPAY && kDir) {
+        Spinor<P>::load(dir.p, vh, h, xs);
+        Spinor<P>::load(dir.r, vh, h, rs);
+        pin(xs);
+        pin(rs);
+    } else if constexpr (XPAY) {
+        Spinor<P>::load(xv, vh, h, xs);
+    }
     cx<R> res[3] = {{0, 0}, {0, 0}, {0, 0}};
     constexpr int K = 16 / S;
-    cx<R> m[K][9], v[K][3];
+    cx<R> m[K][9], v[K][3], rn[K][3];
 #pragma unroll
     for (int u = 0; u < K; ++u) {
         const int s = j + S * u;
@@ -283,6 +303,7 @@ __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
         else if (S * u < 8) load_link<P, 9, kStream>(fat, s, g.lp, h, m[u]);
         else load_link<P, 6, kStream>(naik, s - 8, g.lp, h, m[u]);
         Spinor<P>::load(in, vh, nb, v[u]);
+        if constexpr (kDir && !XPAY) Spinor<P>::load(dir.r, vh, nb, rn[u]);
     }
     // every load is issued before the first of their values is used (left to itself the
     // compiler puts each behind the arithmetic of the one before: 16^4 FP64 17.1 us, not 12.8)
@@ -293,8 +314,34 @@ __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
             asm volatile("" : "+v"(m[u][e].r), "+v"(m[u][e].i));
 #pragma unroll
         for (int e = 0; e < 3; ++e) asm volatile("" : "+v"(v[u][e].r), "+v"(v[u][e].i));
+        if constexpr (kDir && !XPAY) pin(rn[u]);
     }
     if (stop) return;
+    if constexpr (kDir && !XPAY) {
+        const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+        const StepEnd end(dir.st);
+        if (!end.decide(dir.st, fused_total<kSplitThreads>(share), lead, dir.coef, dir.coef_cap,
+                        beta))
+            return;
+        const R b = (R)beta;
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                v[u][e].r = fma(b, v[u][e].r, rn[u][e].r);
+                v[u][e].i = fma(b, v[u][e].i, rn[u][e].i);
+            }
+    }
+    if constexpr (kDir && XPAY) {
+        const R b = (R)beta;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            xs[e].r = fma(b, xs[e].r, rs[e].r);
+            xs[e].i = fma(b, xs[e].i, rs[e].i);
+        }
+        // every lane that reads site h is of this wave and has read it
+        if (live && j == 0) Spinor<P>::store(dir.p, vh, h, xs);
+    }
 #pragma unroll
     for (int u = 0; u < K; ++u) {
         const int s = j + S * u;
@@ -415,20 +462,60 @@ int lds_of(const TuneEntry& t, int P, int vh)
 // FP32) 56.4 / 53.3, 133 MB (24^3x20 FP16 12-real) 56.5 / 52.8; 369 MB (20^4 FP64) 82.8 / 88.6.
 constexpr size_t kCachedLinks = (size_t)200 << 20;
 
-template <int P, int RECON, int S, bool kStream>
+template <int P, int RECON, int S, bool kStream, bool kDir>
 void launch_split(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a, hipStream_t s)
 {
-    const int nb = blocks_for(G.Vh, kSplitThreads / S);
     const int p = a.out_parity;
+    const CGDirection dir = a.dir ? *a.dir : CGDirection{};
+    const int nb = blocks_for(G.Vh, kSplitThreads / S);
     if (a.x)
-        dslash_split_kernel<P, RECON, true, S, kStream><<<nb, kSplitThreads, 0, s>>>(
+        dslash_split_kernel<P, RECON, true, S, kStream, kDir><<<nb, kSplitThreads, 0, s>>>(
             G, p, st.fat[p], st.naik[p], a.in, a.out, a.x, a.a, a.dot_partials, a.gate,
-            st.fat_scale, st.naik_scale, c0);
-    else
-        dslash_split_kernel<P, RECON, false, S, kStream><<<nb, kSplitThreads, 0, s>>>(
+            st.fat_scale, st.naik_scale, c0, dir);
+    else if constexpr (!(kDir && P == KS_F64 && S == 4))   // see launch_split_links
+        dslash_split_kernel<P, RECON, false, S, kStream, kDir><<<nb, kSplitThreads, 0, s>>>(
             G, p, st.fat[p], st.naik[p], a.in, a.out, nullptr, 0.0, nullptr, a.gate, st.fat_scale,
-            st.naik_scale, c0);
+            st.naik_scale, c0, dir);
     KS_HIP(hipGetLastError());
+}
+
+size_t link_bytes(int P, int RECON, int lp)
+{
+    const size_t es = P == KS_F64 ? 16 : P == KS_F32 ? 8 : 4;
+    return (size_t)2 * 8 * (9 + (RECON == 12 ? 6 : 9)) * es * lp;
+}
+
+// Where links stay in the caches a CG step is short, and the launch that writes its direction is a
+// good part of it (FP64 and FP32; a binary16 direction would have to be rounded to its record at
+// every neighbour).  CG step with / without that launch, us: FP64 8^4 14.8 / 12.8, 12^4 20.7 / 19.0, 16^4
+// 36.6 / 34.7, 14x18x16x20 (186 MB) 41.8 / 41.6, 18^4 (242 MB) 60.8 / 63.8; FP32 12^4 15.8 / 13.4, 16^4
+// 24.8 / 22.8, 20^4 (184 MB) 43.2 / 42.0, 20^3x24 (221 MB) 54.6 / 57.9, its 12-real form (184 MB)
+// 44.8 / 44.2.
+bool forms_direction(const TuneEntry& t, int P, int RECON, const Geom& G)
+{
+    return P != KS_F16 && split_of(t, P, G.Vh) > 1 && link_bytes(P, RECON, G.lp) <= kCachedLinks;
+}
+
+template <int P, int RECON, int S>
+void launch_split_links(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a,
+                        hipStream_t s)
+{
+    if constexpr (P != KS_F16) {
+        if (a.dir) {
+            // gathering two FP64 vectors at four lanes per site would leave one wave per SIMD; the
+            // steps that gather one take the same lanes, whose sums have one order
+            constexpr int G8 = P == KS_F64 ? 8 : S;
+            if (a.x && a.dir_begun) launch_split<P, RECON, S, false, true>(st, G, c0, a, s);
+            else if (a.x) launch_split<P, RECON, S, false, false>(st, G, c0, a, s);
+            else if (a.dir_begun) launch_split<P, RECON, G8, false, true>(st, G, c0, a, s);
+            else launch_split<P, RECON, G8, false, false>(st, G, c0, a, s);
+            return;
+        }
+    }
+    if (link_bytes(P, RECON, G.lp) <= kCachedLinks)
+        launch_split<P, RECON, S, false, false>(st, G, c0, a, s);
+    else
+        launch_split<P, RECON, S, true, false>(st, G, c0, a, s);
 }
 
 template <int P, int RECON, int NT, int U>
@@ -459,17 +546,11 @@ void launch_p(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a
 {
     const int split = split_of(t, P, G.Vh);
     t.lds = lds_of(t, P, G.Vh);
-    const size_t links = (size_t)2 * 8 * (9 + (RECON == 12 ? 6 : 9)) * EntrySize<P>::value * G.lp;
-    if (split == 4) {
-        if (links <= kCachedLinks) launch_split<P, RECON, 4, false>(st, G, c0, a, s);
-        else launch_split<P, RECON, 4, true>(st, G, c0, a, s);
-        return;
-    }
-    if (split == 8) {
-        if (links <= kCachedLinks) launch_split<P, RECON, 8, false>(st, G, c0, a, s);
-        else launch_split<P, RECON, 8, true>(st, G, c0, a, s);
-        return;
-    }
+    KS_REQUIRE(!a.dir || forms_direction(t, P, RECON, G), KS_ERR_ARG,
+               "Dslash: this variant does not form the direction");
+    if (split == 4) launch_split_links<P, RECON, 4>(st, G, c0, a, s);
+    else if (split == 8) launch_split_links<P, RECON, 8>(st, G, c0, a, s);
+    if (split > 1) return;
     if (t.nt == 64) launch_nt<P, RECON, 64>(st, G, c0, a, t, s);
     else if (t.nt == 128) launch_nt<P, RECON, 128>(st, G, c0, a, t, s);
     else launch_nt<P, RECON, 256>(st, G, c0, a, t, s);
@@ -496,6 +577,11 @@ int dslash_blocks(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon)
     const TuneEntry& t = g->tune[prec][recon_index(recon)];
     const int split = split_of(t, (int)prec, g->geom.Vh);
     return blocks_for(g->geom.Vh, split > 1 ? kSplitThreads / split : t.nt);
+}
+
+bool dslash_forms_direction(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon)
+{
+    return forms_direction(g->tune[prec][recon_index(recon)], (int)prec, (int)recon, g->geom);
 }
 
 bool dslash_form_built(ks_prec_t prec, ks_recon_t recon, int links_per_pass, int link_access,

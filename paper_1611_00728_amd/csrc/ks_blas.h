@@ -28,6 +28,20 @@ struct CGState {
     int s_iter, s_gate;
 };
 
+// A CG step whose two hopping terms take the direction p = r + beta p of the step before: the first
+// (in = p, which still holds the old direction) ends that step from its |r|^2 partials, as
+// cg_beta_xpay does, and gathers r + beta p; the second (x = p) forms it again at its own sites and
+// stores it to p.
+struct CGDirection {
+    CGState* st;
+    const void* r;
+    void* p;
+    const double* rr_part;
+    int nrr;
+    double* coef;
+    int coef_cap;
+};
+
 void convert_field(int vh, ks_prec_t pin, const void* in, ks_prec_t pout, void* out,
                    const int* gate, hipStream_t s);
 void norm2_partials(int vh, const double* v, double* partials, hipStream_t s);

@@ -264,9 +264,15 @@ struct DslashArgs {
     double a = 0.0;
     double* dot_partials = nullptr;
     const int* gate = nullptr;     // when set and *gate != 0 the launch does nothing
+    // set for the hopping terms of a CG run (variants that dslash_forms_direction names); begun: the
+    // step before left its direction to these two
+    const struct CGDirection* dir = nullptr;
+    bool dir_begun = false;
 };
 void dslash(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, const DslashArgs& a,
             hipStream_t s);
+// whether launches of this variant take DslashArgs::dir
+bool dslash_forms_direction(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon);
 // number of per-block partial sums a Dslash launch of this variant writes
 int dslash_blocks(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon);
 // upper bound of dslash_blocks over every launch configuration

@@ -251,12 +251,19 @@ ks_status_t cg_core(ks_gauge_t g, double sigma, const double* b, double* x,
         cg_reliable(w.partials, w.npart, w.st, initial, s);
         if (P != KS_F64) convert_field(vh, KS_F64, w.r64, P, rs, nullptr, s);
     };
-    auto iteration = [&]() {
+    const CGDirection dir = {w.st, rs, ps, w.rr_part, blocks_for(vh, cg_step_threads(vh)), w.cg_coef,
+                             w.cg_coef_cap};
+    // the steps between two reads of the state hand their directions on
+    const bool hand_on = dslash_forms_direction(g, P, RC);
+    // begun: the step before was left open, its direction still to be formed; open: so is this one's
+    auto iteration = [&](bool begun, bool open) {
         DslashArgs a1;
         a1.out_parity = 1;
         a1.in = ps;
         a1.out = ts;
         a1.gate = &w.st->gate;
+        a1.dir = hand_on ? &dir : nullptr;
+        a1.dir_begun = begun;
         dslash(g, P, RC, a1, s);
         DslashArgs a2;
         a2.out_parity = 0;
@@ -266,9 +273,12 @@ ks_status_t cg_core(ks_gauge_t g, double sigma, const double* b, double* x,
         a2.a = sigma;
         a2.dot_partials = w.partials;
         a2.gate = &w.st->gate;
+        a2.dir = a1.dir;
+        a2.dir_begun = begun;
         dslash(g, P, RC, a2, s);
         cg_update(vh, P, xu, ps, qs, rs, w.st, w.partials, dslash_blocks(g, P, RC), w.rr_part,
                   w.cg_coef, w.cg_coef_cap, s);
+        if (open) return;
         cg_beta_xpay(vh, P, rs, ps, w.st, w.rr_part, w.cg_coef, w.cg_coef_cap, s);
     };
 
@@ -316,7 +326,7 @@ ks_status_t cg_core(ks_gauge_t g, double sigma, const double* b, double* x,
             }
             break;
         }
-        for (int k = 0; k < chunk; ++k) iteration();
+        for (int k = 0; k < chunk; ++k) iteration(hand_on && k > 0, hand_on && k + 1 < chunk);
     }
     flush();   // x = the last iterate also when the loop ended on an error
     read_state(w, s);

@@ -415,3 +415,36 @@ def test_cg_step_blocks(ks, dims):
         torch.cuda.synchronize()
         assert res.stats["iters"] == 6
         assert np.linalg.norm(host(x) - ref) <= tol * np.linalg.norm(ref)
+
+
+# the steps between two reads of the state hand their directions on where the links stay in the
+# caches: eight and four lanes per site, ragged waves and blocks, reliable updates and the step cap
+# inside such a run; FP32 20x20x20x24 is past the line
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 6, 6, 6), (6, 10, 14, 10), (12, 12, 12, 12)])
+@pytest.mark.parametrize("inner", ["f64", "f32"])
+@pytest.mark.parametrize("recon", [18, 12])
+def test_cg_hands_directions_on(ks, dims, inner, recon):
+    """A solve that reads its state after every step forms every direction in a launch of its own;
+    one that reads it after several forms the same bits in the hopping term."""
+    import torch
+    announce("cg directions", dims, inner, recon)
+    g = make_gauge(dims, 0.4, 61)
+    vh = g.volume // 2
+    G = ks.Gauge(dims, g.fat, g.naik)
+    b = dev(gaussian_source(vh, 62))
+    for cap in (7, 1000):
+        runs = []
+        for every in (1, 2, 5, 16):
+            x = zeros_dev((vh, 3))
+            p = ks.default_params(tol=1e-11, inner=ks.PREC[inner], recon=recon, max_iter=cap,
+                                  check_every=every, delta=0.03)
+            res = ks.cg_solve(G, 0.1, b, x, p, raise_on_error=False)
+            torch.cuda.synchronize()
+            a, be = G.cg_coefficients()
+            runs.append((res.status, res.stats["iters"], res.stats["reliable_updates"], host(x),
+                         np.array(a), np.array(be)))
+        for r in runs[1:]:
+            assert r[:3] == runs[0][:3]
+            assert np.array_equal(r[3], runs[0][3])
+            assert np.array_equal(r[4], runs[0][4])
+            assert np.array_equal(r[5], runs[0][5], equal_nan=True)
