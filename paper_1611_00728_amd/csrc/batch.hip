@@ -335,16 +335,34 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void ba
 // Sums over the lattice's tiles of the partials of every RHS (thread j adds tiles j, j + NT,
 // ... in order, then the fixed wave and block order): every block of the lattice gets the
 // same totals bit for bit.
-template <int NT>
+template <int NT, int R>
 __device__ __forceinline__ void lattice_totals(const LatDesc& L, const double* __restrict__ part,
-                                               int R, double tot[4])
+                                               double tot[4])
 {
     __shared__ double red[NT / 64][4];
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int t = L.tile_begin + threadIdx.x; t < L.tile_end; t += NT)
-        for (int r = 0; r < R; ++r) s[r] += part[(size_t)t * R + r];
+    const int end = L.tile_end;
+    constexpr int kAhead = 4;   // loads in flight: one 14.9 us a direction launch, four 13.3, eight 13.4
+    for (int t0 = L.tile_begin + threadIdx.x; t0 < end; t0 += kAhead * NT) {
+        double v[kAhead][R];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) s[r] = wave_sum(s[r]);
+        for (int u = 0; u < kAhead; ++u) {
+            const size_t t = min(t0 + u * NT, end - 1);
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[u][r] = part[t * R + r];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+            for (int r = 0; r < R; ++r) asm volatile("" : "+v"(v[u][r]));
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (t0 + u * NT < end)
+#pragma unroll
+                for (int r = 0; r < R; ++r) s[r] += v[u][r];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[r] = wave_sum(s[r]);
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[threadIdx.x >> 6][r] = s[r];
@@ -387,7 +405,7 @@ __global__ __launch_bounds__(NT) void batch_update_kernel(
         const int mode = pairs[L.pair0].s_mode;
         if (mode == 0) continue;
         if (tl.x != cached) {
-            lattice_totals<NT>(L, part, R, tot);
+            lattice_totals<NT, R>(L, part, tot);
             cached = tl.x;
         }
         const bool lead = tl.y == 0 && threadIdx.x == 0;
@@ -557,7 +575,7 @@ __global__ __launch_bounds__(NT) void batch_direction_kernel(
             continue;
         }
         if (tl.x != cached) {
-            lattice_totals<NT>(L, part2, R, tot);
+            lattice_totals<NT, R>(L, part2, tot);
             cached = tl.x;
         }
         bool live[R], nonfin[R], due[R];
