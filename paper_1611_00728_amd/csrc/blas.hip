@@ -12,15 +12,6 @@ namespace {
 constexpr int kFinish = 1024;
 
 // Fixed-order sum: thread t adds partials t, t + 1024, ... in order, then a fixed tree.
-__global__ __launch_bounds__(kFinish) void reduce_sum_kernel(const double* __restrict__ in, int n,
-                                                             double* __restrict__ out)
-{
-    double s = 0.0;
-    for (int k = threadIdx.x; k < n; k += kFinish) s += in[k];
-    s = block_sum<kFinish>(s);
-    if (threadIdx.x == 0) *out = s;
-}
-
 __global__ __launch_bounds__(kFinish) void reduce_max_kernel(const double* __restrict__ in, int n,
                                                              double* __restrict__ out)
 {
@@ -309,12 +300,6 @@ __global__ void finish_to_kernel(const double* __restrict__ part, int n, double*
 }
 
 }  // namespace
-
-void reduce_sum(const double* partials, int n, double* out, hipStream_t s)
-{
-    reduce_sum_kernel<<<1, kFinish, 0, s>>>(partials, n, out);
-    KS_HIP(hipGetLastError());
-}
 
 void reduce_max(const double* partials, int n, double* out, hipStream_t s)
 {

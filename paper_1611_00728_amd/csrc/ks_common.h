@@ -243,8 +243,7 @@ inline int blocks_for(long n, int nt = kBlock) { return (int)((n + nt - 1) / nt)
 
 // ------------------------------------------------------------------ reductions (blas.hip)
 
-// Deterministic sum of `n` doubles (fixed order), result written to *out (device).
-void reduce_sum(const double* partials, int n, double* out, hipStream_t s);
+// Largest of `n` non-negative doubles, result written to *out (device).
 void reduce_max(const double* partials, int n, double* out, hipStream_t s);
 
 // ------------------------------------------------------------------ launchers

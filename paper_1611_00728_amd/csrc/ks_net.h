@@ -25,9 +25,6 @@ struct NetBuffers {
     float2* grad[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     // matrix-core path: levels 1..3 as binary16 records [parity][6][Vh] x 16 bytes
     __half* act16[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-    int npart = 0;
-    double* part = nullptr;
-    double* wpart = nullptr;
 };
 
 struct NetCtx {
@@ -38,6 +35,8 @@ struct NetCtx {
     double* adam_v = nullptr;
     double* grad = nullptr;     // gradient of the free weights
     double* grad4 = nullptr;    // gradient of the four applied layers' weights
+    double* part = nullptr;     // partial sums of a gradient call, part_size reals
+    size_t part_size = 0;
     double* scal = nullptr;
     double* host = nullptr;     // pinned
     int step = 0;               // Adam steps taken

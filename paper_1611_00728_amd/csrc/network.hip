@@ -18,6 +18,7 @@
 #include <cstring>
 #include <vector>
 
+#include "ks_cg_step.h"
 #include "ks_device.h"
 #include "ks_net.h"
 #include "ks_solvers.h"
@@ -41,7 +42,7 @@ __device__ __forceinline__ const float4* act_pair(const float4* a, int par, int 
     return a + (size_t)((par * 3 + k) * 4 + q) * vh;
 }
 
-// even half of a one-channel level, as a vector the first layer reads and the last one writes
+// even half of a one-channel level, as a vector that a first layer reads
 struct ActPlanes {
     using R = float;
     __device__ static __forceinline__ void load(const void* b, int vh, int h, cx<R> v[3])
@@ -52,12 +53,6 @@ struct ActPlanes {
             const float2 t = p[(size_t)k * vh + h];
             v[k] = {t.x, t.y};
         }
-    }
-    __device__ static __forceinline__ void store(void* b, int vh, int h, const cx<R> v[3])
-    {
-        float2* p = static_cast<float2*>(b);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) p[(size_t)k * vh + h] = make_float2(v[k].r, v[k].i);
     }
 };
 
@@ -468,7 +463,7 @@ __global__ __launch_bounds__(kNT, 3) void net_wgrad8_kernel(Geom g, const float4
         __syncthreads();
         for (int e = tid; e < COUT * 16; e += kNT) {
             const int reim = e & 1, ci = (e >> 1) % 8, co = e / 16;
-            partials[(size_t)blockIdx.x * NV + ((co * 8 + ci) * 9 + p0 + q) * 2 + reim] =
+            partials[(size_t)blockIdx.x * NV + ((co * 8 + ci) * 9 + p0 + q) * 2 + reim] +=
                 wgrad_value(red, 2 * co, 2 * ci, reim);
         }
     }
@@ -564,13 +559,13 @@ __global__ __launch_bounds__(kNT) void net_wgrad1_kernel(Geom g, const float2* _
         const int np = q ? 8 : 1;
         for (int e = tid; e < 8 * np * 2; e += kNT) {
             const int reim = e & 1, p = (e >> 1) % np, co = (e >> 1) / np;
-            partials[(size_t)blockIdx.x * NV + (co * 9 + (q ? p + 1 : 0)) * 2 + reim] =
+            partials[(size_t)blockIdx.x * NV + (co * 9 + (q ? p + 1 : 0)) * 2 + reim] +=
                 wgrad_value(red, 2 * co, 2 * p, reim);
         }
     }
 }
 
-// grad[k] += sum_b partials[b][k] for 16 values per block: slice j of a value's 64 threads adds
+// grad[k] = sum_b partials[b][k] for 16 values per block: slice j of a value's 64 threads adds
 // partials j, j + 64, ..., then the slices in a fixed order.  (64 values and 16 slices per block
 // leave the 512 x 1152 partials of an 8 -> 8 layer to 18 CUs: 11.1 us.)
 __global__ __launch_bounds__(1024) void net_grad_finish_kernel(const double* __restrict__ partials,
@@ -591,7 +586,7 @@ __global__ __launch_bounds__(1024) void net_grad_finish_kernel(const double* __r
         double v = 0.0;
 #pragma unroll
         for (int q = 0; q < 16; ++q) v += red[q][l];
-        grad[k] += v;
+        grad[k] = v;
     }
 }
 
@@ -607,37 +602,46 @@ __global__ void net_adjoint_weights_kernel(const float2* __restrict__ w, float2*
     wa[(ci * cout + o) * 9 + pb] = make_float2(v.x, -v.y);
 }
 
-// network input: the even sites of level 0 from a complex128 [Vh][3] vector
-__global__ void net_embed_kernel(int vh, const double2* __restrict__ src, float2* __restrict__ act)
+// One pair's x and b (complex128 [Vh][3]): the even sites of the network's input b, and partials of
+// x^+ A x = Re<x, b>
+__global__ __launch_bounds__(kNT) void net_pair_kernel(int vh, const double2* __restrict__ x,
+                                                       const double2* __restrict__ b,
+                                                       float2* __restrict__ act,
+                                                       double* __restrict__ partials)
 {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= vh) return;
+    const int h = blockIdx.x * kNT + threadIdx.x;
+    double s = 0.0;
+    if (h < vh)
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double2 v = src[(size_t)h * 3 + k];
-        act[(size_t)k * vh + h] = make_float2((float)v.x, (float)v.y);
-    }
+        for (int k = 0; k < 3; ++k) {
+            const double2 u = x[(size_t)h * 3 + k], v = b[(size_t)h * 3 + k];
+            s += u.x * v.x + u.y * v.y;
+            act[(size_t)k * vh + h] = make_float2((float)v.x, (float)v.y);
+        }
+    s = block_sum<kNT>(s);
+    if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-// A-norm loss term of one pair and the output gradient: with y = N(b) (even sites of the last
-// layer) and ay = A y (FP64 planes), partial sums of Re<y - x, A y - b> = (y - x)^+ A (y - x)
+// A-norm loss term of one pair and the output gradient: with y = N(b) and ay = A y (FP64 planes, even
+// sites), x^+ A x from the partials xax_part (as many as blocks here), partial sums of Re<y - x, A y - b> = (y - x)^+ A (y - x)
 // (A x = b) and G = 2 (A y - b) / (x^+ A x npairs) on even sites (the Wirtinger gradient of the
 // pair's loss is 2 A (y - x) over its normalisation).
-__global__ __launch_bounds__(kNT) void net_anorm_loss_kernel(int vh, const float2* __restrict__ y,
+__global__ __launch_bounds__(kNT) void net_anorm_loss_kernel(int vh, const double2* __restrict__ y,
                                                              const double2* __restrict__ ay,
                                                              const double2* __restrict__ b,
                                                              const double2* __restrict__ x,
-                                                             const double* __restrict__ xax,
+                                                             const double* __restrict__ xax_part,
                                                              int npairs, float2* __restrict__ gy,
                                                              double* __restrict__ partials)
 {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
+    const int h = blockIdx.x * kNT + threadIdx.x;
+    const double xax = fused_total<kNT>(fused_load<kNT>(xax_part, gridDim.x));
     double s = 0.0;
     if (h < vh) {
-        const double coef = 2.0 / (*xax * npairs);
+        const double coef = 2.0 / (xax * npairs);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const float2 o = y[(size_t)k * vh + h];
+            const double2 o = y[(size_t)k * vh + h];
             const double2 a = ay[(size_t)k * vh + h];
             const double2 bv = b[(size_t)h * 3 + k];
             const double2 xv = x[(size_t)h * 3 + k];
@@ -650,33 +654,21 @@ __global__ __launch_bounds__(kNT) void net_anorm_loss_kernel(int vh, const float
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-// even sites of the last layer (FP32 planes) -> FP64 planes [3][Vh]
-__global__ void net_out_f64_kernel(int vh, const float2* __restrict__ y, double2* __restrict__ out)
-{
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= vh) return;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const float2 v = y[(size_t)k * vh + h];
-        out[(size_t)k * vh + h] = make_double2(v.x, v.y);
-    }
-}
+// Sums of a chunk of pairs: block 2 k the partials of x^+ A x of pair k, block 2 k + 1 those of its
+// loss, lists of n[k] partials at a pitch of `pitch`.
+constexpr int kPairChunk = 32;
 
-// partials of Re<x, b> of two complex128 [Vh][3] vectors
-__global__ __launch_bounds__(kNT) void net_rdot_kernel(int vh, const double2* __restrict__ x,
-                                                       const double2* __restrict__ b,
-                                                       double* __restrict__ partials)
+struct PairCounts {
+    int n[kPairChunk];
+};
+
+__global__ __launch_bounds__(kNT) void net_pair_sums_kernel(const double* __restrict__ partials,
+                                                            int pitch, PairCounts c,
+                                                            double* __restrict__ out)
 {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    double s = 0.0;
-    if (h < vh)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const double2 u = x[(size_t)h * 3 + k], v = b[(size_t)h * 3 + k];
-            s += u.x * v.x + u.y * v.y;
-        }
-    s = block_sum<kNT>(s);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s;
+    const double s = fused_total<kNT>(
+        fused_load<kNT>(partials + (size_t)blockIdx.x * pitch, c.n[blockIdx.x / 2]));
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 __device__ __forceinline__ int reversed_path(int p) { return p == 0 ? 0 : (p <= 4 ? p + 4 : p - 4); }
@@ -795,31 +787,34 @@ void expand_weights(NetCtx& n, hipStream_t s)
 // 256 / 512 blocks: 16^4 25.1 / 28.5 us, 32^4 425 / 462 us; the 1 -> 8 layer's 101 / 137 us)
 constexpr int kWgrad8Blocks = 256;
 
+// Blocks of a layer's weight-gradient kernel on a lattice.
+int wgrad_blocks(int cin, int cout, const Geom& G)
+{
+    const int tiles = cin == 1 ? 2 * blocks_for(G.Vh, kWTile)
+                               : blocks_for(cout == 8 ? 2L * G.Vh : G.Vh, kWTile);
+    return std::min(tiles, cin == 1 ? kWgradBlocks : kWgrad8Blocks);
+}
+
+// Adds the pair's weight gradient to each block's sums in `part`: the blocks' sums run over all
+// pairs and are added up once (a finishing launch per pair and layer was 23 us of a pair's 261 at 16^4).
 template <int CIN, int COUT>
-void wgrad(NetBuffers& B, ks_gauge_t g, const float2* in, const float2* gy, double* grad,
-           hipStream_t s)
+void wgrad(ks_gauge_t g, const float2* in, const float2* gy, double* part, hipStream_t s)
 {
     const LinkStore& st = g->store[KS_F32][0];
     const Geom& G = g->geom;
-    constexpr int NV = COUT * CIN * 9 * 2;
-    const int tiles = CIN == 1 ? 2 * blocks_for(G.Vh, kWTile)
-                               : blocks_for(COUT == 8 ? 2L * G.Vh : G.Vh, kWTile);
-    const int nb = std::min(tiles, CIN == 1 ? kWgradBlocks : kWgrad8Blocks);
+    const int nb = wgrad_blocks(CIN, COUT, G);
     const bool cached = links_cached(G);
     if constexpr (CIN == 1) {
         const float4* g4 = reinterpret_cast<const float4*>(gy);
-        if (cached) net_wgrad1_kernel<false><<<nb, kNT, 0, s>>>(G, in, g4, st.fat[1], B.wpart);
-        else net_wgrad1_kernel<true><<<nb, kNT, 0, s>>>(G, in, g4, st.fat[1], B.wpart);
+        if (cached) net_wgrad1_kernel<false><<<nb, kNT, 0, s>>>(G, in, g4, st.fat[1], part);
+        else net_wgrad1_kernel<true><<<nb, kNT, 0, s>>>(G, in, g4, st.fat[1], part);
     } else {
         const float4* x = reinterpret_cast<const float4*>(in);
         if (cached)
-            net_wgrad8_kernel<COUT, false><<<dim3(nb, 3), kNT, 0, s>>>(G, x, gy, st.fat[0], st.fat[1], B.wpart);
+            net_wgrad8_kernel<COUT, false><<<dim3(nb, 3), kNT, 0, s>>>(G, x, gy, st.fat[0], st.fat[1], part);
         else
-            net_wgrad8_kernel<COUT, true><<<dim3(nb, 3), kNT, 0, s>>>(G, x, gy, st.fat[0], st.fat[1], B.wpart);
+            net_wgrad8_kernel<COUT, true><<<dim3(nb, 3), kNT, 0, s>>>(G, x, gy, st.fat[0], st.fat[1], part);
     }
-    KS_HIP(hipGetLastError());
-    static_assert(NV % 16 == 0, "values per block of the finishing kernel");
-    net_grad_finish_kernel<<<NV / 16, 1024, 0, s>>>(B.wpart, nb, NV, grad);
     KS_HIP(hipGetLastError());
 }
 
@@ -865,12 +860,9 @@ NetBuffers& net_buffers(NetCtx& n, const Geom& g)
         const size_t site = (size_t)2 * 3 * g.Vh * sizeof(float2);   // one channel, both parities
         const int ch[5] = {1, 8, 8, 8, 1};
         for (int l = 0; l < 5; ++l) {
-            B.act[l] = static_cast<float2*>(device_alloc(site * ch[l]));
+            if (l < 4) B.act[l] = static_cast<float2*>(device_alloc(site * ch[l]));
             B.grad[l] = static_cast<float2*>(device_alloc(site * ch[l]));
         }
-        B.npart = blocks_for(g.Vh, kNT);
-        B.part = static_cast<double*>(device_alloc(sizeof(double) * (B.npart + 8)));
-        B.wpart = static_cast<double*>(device_alloc(sizeof(double) * kWgradBlocks * 8 * 8 * 9 * 2));
         B.vh = g.Vh;
     }
     return B;
@@ -885,8 +877,6 @@ void net_free(NetCtx* n)
             device_free(kv.second.grad[l]);
             device_free(kv.second.act16[l]);
         }
-        device_free(kv.second.part);
-        device_free(kv.second.wpart);
     }
     device_free(n->w64);
     device_free(n->w32);
@@ -896,6 +886,7 @@ void net_free(NetCtx* n)
     device_free(n->grad);
     device_free(n->grad4);
     device_free(n->scal);
+    device_free(n->part);
     device_free(n->wmma);
     if (n->host) (void)hipHostFree(n->host);
     delete n;
@@ -989,12 +980,36 @@ void net_apply_spinor(NetCtx& n, ks_gauge_t g, ks_prec_t prec, const void* r, vo
         forward<Spinor<KS_F32>, Spinor<KS_F32>>(n, B, g, r, z, s, in_scale, gate);
 }
 
-// A-norm loss of the pairs and its gradient: the four applied layers' gradients accumulate in
-// n.grad4 (zeroed first), then fold into the free weights' gradient n.grad.
+// A-norm loss of the pairs and its gradient: the four applied layers' gradients, summed over the
+// pairs, go to n.grad4 and fold into the free weights' gradient n.grad.
 double net_loss_grad(NetCtx& n, int npairs, const ks_gauge_t* gauges, const double* sigma,
                      const double* const* b, const double* const* x, hipStream_t s)
 {
-    KS_HIP(hipMemsetAsync(n.grad4, 0, sizeof(double) * 2 * kNetLayerWeights, s));
+    // n.part: per layer the blocks' weight gradients (cleared here), then for each pair of a chunk
+    // the partials of x^+ A x and of its loss
+    int blocks[4] = {0, 0, 0, 0}, pitch = 0;
+    for (int j = 0; j < npairs; ++j) {
+        const Geom& G = gauges[j]->geom;
+        for (int l = 0; l < 4; ++l)
+            blocks[l] = std::max(blocks[l], wgrad_blocks(kLayerIn[l], kLayerOut[l], G));
+        pitch = std::max(pitch, blocks_for(G.Vh, kNT));
+    }
+    size_t at[5] = {0};
+    int nv[4];
+    for (int l = 0; l < 4; ++l) {
+        nv[l] = kLayerIn[l] * kLayerOut[l] * 9 * 2;
+        at[l + 1] = at[l] + (size_t)blocks[l] * nv[l];
+    }
+    const size_t need = at[4] + (size_t)std::min(npairs, kPairChunk) * 2 * pitch;
+    if (n.part_size < need) {
+        device_free(n.part);
+        n.part = nullptr;
+        n.part_size = 0;
+        n.part = static_cast<double*>(device_alloc(sizeof(double) * need));
+        n.part_size = need;
+    }
+    double* pair_part = n.part + at[4];
+    KS_HIP(hipMemsetAsync(n.part, 0, sizeof(double) * at[4], s));
     const float2* w = reinterpret_cast<const float2*>(n.w32);
     float2* wa = reinterpret_cast<float2*>(n.wadj);
     for (int l = 1; l < 4; ++l) {
@@ -1004,54 +1019,55 @@ double net_loss_grad(NetCtx& n, int npairs, const ks_gauge_t* gauges, const doub
     }
     KS_HIP(hipGetLastError());
     // x^+ A x and the loss of a pair stay on the device while its kernels are queued; the host
-    // reads those of up to kChunk pairs together (reading each when it was needed left the GPU
+    // reads those of up to kPairChunk pairs together (reading each when it was needed left the GPU
     // idle twice per pair, some 35 us)
-    constexpr int kChunk = 32;
     double loss = 0.0;
+    PairCounts counts{};
     for (int j = 0; j < npairs; ++j) {
-        double* sc = n.scal + 2 * (j % kChunk);
+        const int c = j % kPairChunk;
         ks_gauge_t g = gauges[j];
         gauge_prepare(g, KS_F32, KS_RECON_18, s);
         Workspace& ws = workspace(g);
         NetBuffers& B = net_buffers(n, g->geom);
         const int vh = g->geom.Vh;
         const int nb = blocks_for(vh, kNT);
+        counts.n[c] = nb;
+        double* xax = pair_part + (size_t)2 * c * pitch;
         const double2* bj = reinterpret_cast<const double2*>(b[j]);
         const double2* xj = reinterpret_cast<const double2*>(x[j]);
-        // x^+ A x = Re<x, b>
-        net_rdot_kernel<<<nb, kNT, 0, s>>>(vh, xj, bj, B.part);
-        reduce_sum(B.part, nb, sc, s);
-        net_embed_kernel<<<blocks_for(vh), kBlock, 0, s>>>(vh, bj, B.act[0]);
-        forward<ActPlanes, ActPlanes>(n, B, g, B.act[0], B.act[4], s);
-        // A y in FP64 on the pair's lattice
-        net_out_f64_kernel<<<blocks_for(vh), kBlock, 0, s>>>(vh, B.act[4],
-                                                             reinterpret_cast<double2*>(ws.r64));
+        net_pair_kernel<<<nb, kNT, 0, s>>>(vh, xj, bj, B.act[0], xax);
+        // y = N(b), written as FP64 planes for A y in FP64 on the pair's lattice
+        forward<ActPlanes, Spinor<KS_F64>>(n, B, g, B.act[0], ws.r64, s);
         apply_A64(g, sigma[j], ws.r64, ws.ax64, s, nullptr);
-        net_anorm_loss_kernel<<<nb, kNT, 0, s>>>(vh, B.act[4],
+        net_anorm_loss_kernel<<<nb, kNT, 0, s>>>(vh, reinterpret_cast<const double2*>(ws.r64),
                                                  reinterpret_cast<const double2*>(ws.ax64), bj, xj,
-                                                 sc, npairs, B.grad[4], B.part);
-        reduce_sum(B.part, nb, sc + 1, s);
+                                                 xax, npairs, B.grad[4], xax + pitch);
+        KS_HIP(hipGetLastError());
         // backward: weight gradients and the adjoint layers
-        double* gr = n.grad4;
-        wgrad<8, 1>(B, g, B.act[3], B.grad[4], gr + 2 * layer_weight_offset(3), s);
+        wgrad<8, 1>(g, B.act[3], B.grad[4], n.part + at[3], s);
         mix_layer<1, ActPlanes>(g, B.grad[4], B.grad[3], wa + layer_weight_offset(3), s);
-        wgrad<8, 8>(B, g, B.act[2], B.grad[3], gr + 2 * layer_weight_offset(2), s);
+        wgrad<8, 8>(g, B.act[2], B.grad[3], n.part + at[2], s);
         mix_layer<8, void>(g, B.grad[3], B.grad[2], wa + layer_weight_offset(2), s);
-        wgrad<8, 8>(B, g, B.act[1], B.grad[2], gr + 2 * layer_weight_offset(1), s);
+        wgrad<8, 8>(g, B.act[1], B.grad[2], n.part + at[1], s);
         mix_layer<8, void>(g, B.grad[2], B.grad[1], wa + layer_weight_offset(1), s);
-        wgrad<1, 8>(B, g, B.act[0], B.grad[1], gr + 2 * layer_weight_offset(0), s);
-        if (j % kChunk == kChunk - 1 || j == npairs - 1) {
-            const int j0 = j - j % kChunk;
-            KS_HIP(hipMemcpyAsync(n.host, n.scal, sizeof(double) * 2 * (j - j0 + 1),
+        wgrad<1, 8>(g, B.act[0], B.grad[1], n.part + at[0], s);
+        if (c == kPairChunk - 1 || j == npairs - 1) {
+            net_pair_sums_kernel<<<2 * (c + 1), kNT, 0, s>>>(pair_part, pitch, counts, n.scal);
+            KS_HIP(hipGetLastError());
+            KS_HIP(hipMemcpyAsync(n.host, n.scal, sizeof(double) * 2 * (c + 1),
                                   hipMemcpyDeviceToHost, s));
             KS_HIP(hipStreamSynchronize(s));
-            for (int k = j0; k <= j; ++k) {
-                const double xax = n.host[2 * (k - j0)];
-                KS_REQUIRE(xax > 0, KS_ERR_ARG, "network training: pair %d has Re<x, b> <= 0", k);
-                loss += n.host[2 * (k - j0) + 1] / (xax * npairs);
+            for (int k = 0; k <= c; ++k) {
+                const double q = n.host[2 * k];
+                KS_REQUIRE(q > 0, KS_ERR_ARG, "network training: pair %d has Re<x, b> <= 0",
+                           j - c + k);
+                loss += n.host[2 * k + 1] / (q * npairs);
             }
         }
     }
+    for (int l = 0; l < 4; ++l)
+        net_grad_finish_kernel<<<nv[l] / 16, 1024, 0, s>>>(n.part + at[l], blocks[l], nv[l],
+                                                           n.grad4 + 2 * layer_weight_offset(l));
     net_fold_kernel<<<blocks_for(kNetWeights, 256), 256, 0, s>>>(
         reinterpret_cast<const double2*>(n.grad4), reinterpret_cast<double2*>(n.grad));
     KS_HIP(hipGetLastError());

@@ -460,3 +460,22 @@ def test_gradient_of_many_pairs(ks):
         assert e.value.code == -1 and "pair %d" % j in str(e.value)
     again, _ = net.loss_grad([G] * n, sig, bd, xd)
     assert again == loss
+
+
+def test_gradient_over_lattices_of_several_sizes(ks):
+    """One call over lattices whose kernels run from one block to the most they take (the blocks'
+    gradient sums run over all pairs, whatever each lattice's number of blocks), after a larger
+    call and after a smaller one: the mean of the pairs' own (FP64 sums of FP32 passes: 1e-5)."""
+    announce("net pairs of several sizes")
+    net = ks.Net(flatten_weights(random_net(5005)))
+    pairs = []
+    for k, dims in enumerate([(4, 4, 4, 4), (12, 12, 12, 12), (6, 4, 6, 4), (8, 8, 8, 10)]):
+        g = make_gauge(dims, 0.4, 86 + k)
+        x = gaussian_source(g.volume // 2, 340 + k)
+        pairs.append((ks.Gauge(dims, g.fat, g.naik), 0.1 + 0.05 * k,
+                      dev(oracle.apply_A(g, 0.1 + 0.05 * k, x)), dev(x)))
+    one = [net.loss_grad([G], [s], [b], [x]) for G, s, b, x in pairs]
+    for pick in ([0, 1, 2, 3], [2, 0], [3, 2, 1]):
+        loss, grad = net.loss_grad(*[[pairs[k][f] for k in pick] for f in range(4)])
+        assert abs(loss - np.mean([one[k][0] for k in pick])) <= 1e-12 * loss
+        assert rel_l2(grad, np.mean([one[k][1] for k in pick], axis=0)) <= 1e-5
