@@ -1028,11 +1028,11 @@ def main():
     msr["lattice"] = list(MS_DIMS)
     fsec = float(np.median(force_runs))
     # per term: import (48 B read + 48 written per even site) and its share of the multi-vector
-    # FP64 hopping term (links, 2304 B per odd site, read once per pass of up to five terms; the
+    # FP64 hopping term (links, 2304 B per odd site, read once per pass of up to ten terms; the
     # term's input and output, 96 B); outer products: both forces written (2 x 4 x 144 B per
     # site) and each term's vector read once per site (48 B)
     nt_ = len(ms_sigma)
-    fpasses = -(-nt_ // 5)
+    fpasses = -(-nt_ // 10)
     fbytes = (nt_ * ms_vh * (96 + 96) + fpasses * ms_vh * 2304 +
               fvol * (2 * 4 * 144 + nt_ * 48))
     # least data: the odd-site links once (2304 B per odd site), each term's solution once
@@ -1047,7 +1047,7 @@ def main():
                     "note": "link derivative of the nine-term rational action from the "
                             "multi-shift solutions, fat and Naik links, FP64; the access model "
                             "also counts the odd images of the solutions written and read back "
-                            "and the links read once per pass of five terms"}
+                            "and the links read once per pass of ten terms"}
     msr["shifts"] = "sigma_i = 4 m_i^2, m_i = geomspace(0.002, 0.5, 9), tol 1e-9 per shift"
 
     lmed = float(np.median([d for d, _ in learned_runs]))
