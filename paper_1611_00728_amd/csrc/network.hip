@@ -301,14 +301,19 @@ __global__ __launch_bounds__(256) void net_last_kernel(Geom geo, const float4* _
 // sites of one colour per step.  A block walks tiles of 64 sites; a thread transports one
 // channel pair of one site per path (the next path's link and vectors are loaded meanwhile) and
 // stages it in LDS in rows of the site's 16 reals, from which the fragments are read; wave w
-// takes the products of sites 16 w .. 16 w + 15.  Its 12 steps per path and tile (48 products
-// per sum) start from zero and are added to FP64 registers; the waves' sums are combined in
-// FP64 in a fixed order, and the block writes one partial per value.  Against every thread
+// takes the products of sites 16 w .. 16 w + 15.  Of its 12 steps per path and tile each
+// wgrad_steps start from zero and are added to FP64 registers: 48 products per FP32 sum between
+// layers of eight channels, 12 where a layer has one (few values, whose FP64 additions cost
+// nothing beside the transports).  The waves' sums are combined in FP64 in a fixed order, and
+// the block writes one partial per value.  Against every thread
 // multiplying its slice of the sites from LDS for one (c, c'): 8 -> 8 at 16^4 55 -> 25 us, 8 -> 1
 // 39 -> 14.5, 1 -> 8 33 -> 8.9.
 constexpr int kWTile = 64;
 constexpr int kWPitch = 20;                // floats per staged row of 16 (bank spread)
 constexpr int kWStage = 3 * kWTile * kWPitch;
+
+// matrix-core steps (of four sites and one colour) per FP32 sum; channels: the fewer of a layer's two
+__host__ __device__ constexpr int wgrad_steps(int channels) { return channels == 8 ? 12 : 3; }
 
 // v, or zeros (by component: a choice between two structures would go through scratch memory)
 __device__ __forceinline__ float4 keep_if(bool on, float4 v)
@@ -448,9 +453,12 @@ __global__ __launch_bounds__(kNT, 3) void net_wgrad8_kernel(Geom g, const float4
             for (int s = 0; s < 12; ++s) {
                 const int row = (s % 3) * kWTile + 16 * wave + 4 * (s / 3) + kk;
                 d = mfma4(a[s], us[buf][row * kWPitch + n], d);
-            }
+                if ((s + 1) % wgrad_steps(COUT) == 0) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[q][r] += (double)d[r];
+                    for (int r = 0; r < 4; ++r) acc[q][r] += (double)d[r];
+                    d = {0.f, 0.f, 0.f, 0.f};
+                }
+            }
             buf ^= 1;
         }
     }
@@ -544,11 +552,14 @@ __global__ __launch_bounds__(kNT) void net_wgrad1_kernel(Geom g, const float2* _
         for (int s = 0; s < 12; ++s) {
             const int row = (s % 3) * kWTile + 16 * wave + 4 * (s / 3) + kk;
             d = mfma4(gs[row * kWPitch + n], us[row * kWPitch + n], d);
-        }
+            if ((s + 1) % wgrad_steps(1) == 0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            acc[0][r] += par ? 0.0 : (double)d[r];
-            acc[1][r] += par ? (double)d[r] : 0.0;
+                for (int r = 0; r < 4; ++r) {
+                    acc[0][r] += par ? 0.0 : (double)d[r];
+                    acc[1][r] += par ? (double)d[r] : 0.0;
+                }
+                d = {0.f, 0.f, 0.f, 0.f};
+            }
         }
     }
     constexpr int NV = 8 * 9 * 2;

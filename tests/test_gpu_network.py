@@ -479,3 +479,26 @@ def test_gradient_over_lattices_of_several_sizes(ks):
         loss, grad = net.loss_grad(*[[pairs[k][f] for k in pick] for f in range(4)])
         assert abs(loss - np.mean([one[k][0] for k in pick])) <= 1e-12 * loss
         assert rel_l2(grad, np.mean([one[k][1] for k in pick], axis=0)) <= 1e-5
+
+
+def test_one_channel_gradient_keeps_small_products(ks):
+    """The weight gradients of the layers with one channel leave FP32 after 12 products.  Without
+    links and with identity weights N b = b, A = sigma, and both one-channel layers' gradients of
+    the identity weight are coef * (sigma - 1) * sum |b|^2 = sum |b|^2.  Of every 16 sites one
+    holds 2^14, three nothing and twelve ones: a sum that runs over all of them in FP32 drops the
+    ones beside 2^28; 12 products (four sites) at a time every sum is a whole number below 2^53
+    and exact."""
+    announce("net one-channel gradient")
+    dims = (8, 8, 8, 8)
+    vh = 2048
+    links = np.zeros((4, 2 * vh, 3, 3), dtype=np.complex128)
+    G = ks.Gauge(dims, links, links)
+    b = np.zeros((vh, 3), dtype=np.complex128)
+    b.reshape(-1, 16, 3)[:, 4:] = 1.0
+    b[::16, 0] = 2.0 ** 14
+    x = np.zeros_like(b)
+    x[4, 0] = 2.0                              # x^+ A x = Re<x, b> = 2: the gradient's factor is 1
+    w = np.zeros(ks.NET_WEIGHTS, dtype=np.complex128)
+    w[0] = w[8 * 9] = 1.0                      # channel 0 -> 0 of both free layers, identity path
+    _, grad = ks.Net(w).loss_grad([G], [2.0], [dev(b)], [dev(x)])
+    assert grad[0] == 2 * np.sum(np.abs(b) ** 2)
