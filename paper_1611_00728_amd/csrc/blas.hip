@@ -166,6 +166,11 @@ __global__ __launch_bounds__(NT) void cg_update_kernel(int vh, void* __restrict_
     // on breakdown), and a block that sees that skips the step as the breakdown test would
     __shared__ int gated;
     if (threadIdx.x == 0) gated = st->gate;
+    __syncthreads();
+    if (gated) {
+        if (lead) st->s_gate = 1;
+        return;
+    }
     double share = fused_load<NT>(pap_part, npap);
     const double rho = st->rho;
     const int h = blockIdx.x * NT + threadIdx.x;
@@ -182,10 +187,6 @@ __global__ __launch_bounds__(NT) void cg_update_kernel(int vh, void* __restrict_
         pin(xv);
     }
     const double pap = fused_total<NT>(share);
-    if (gated) {
-        if (lead) st->s_gate = 1;
-        return;
-    }
     const bool ok = isfinite(pap) && pap > 0.0;
     if (lead) {
         st->pAp = pap;
@@ -239,6 +240,7 @@ __global__ __launch_bounds__(NT) void cg_beta_xpay_kernel(int vh, const void* __
     using R = typename St<P>::R;
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
     const StepEnd end(st);
+    if (end.stop) return;
     const double share = fused_load<NT>(rr_part, nrr);
     const int h = blockIdx.x * NT + threadIdx.x;
     cx<R> rv[3], pv[3];
@@ -248,7 +250,6 @@ __global__ __launch_bounds__(NT) void cg_beta_xpay_kernel(int vh, const void* __
         pin(rv);
         pin(pv);
     }
-    if (end.stop) return;
     double beta;
     if (!end.decide(st, fused_total<NT>(share), lead, coef, coef_cap, beta) || h >= vh) return;
     const R b = (R)beta;

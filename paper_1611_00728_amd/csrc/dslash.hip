@@ -256,15 +256,16 @@ __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
     static_assert(S == 4 || S == 8, "a lane's slots j + S u lie in one half of the 16 for each u");
     constexpr int kSites = 64 / S;                       // per wave
     constexpr int kBlockSites = kSplitThreads / S;
-    // the gate's load overlaps the others: a launch that it stops has read links for nothing,
-    // one that it lets through does not wait for it first
-    int stop;
+    // the gate before anything else: after a reliable update falls due, up to check_every steps
+    // are stopped here, and links read ahead of it would be read for nothing (CG with FP32 inner
+    // steps, 20^4, check_every 64: 18.4 ms with one thread per site, 30.9 with the links ahead of
+    // the gate, 15.1 behind it; waiting for it costs 8^4 FP64 1 %)
     double share = 0.0, beta = 0.0;
     if constexpr (kDir && !XPAY) {
-        stop = dir.st->s_gate;
+        if (dir.st->s_gate) return;
         share = fused_load<kSplitThreads>(dir.rr_part, dir.nrr);
     } else {
-        stop = gate ? *gate : 0;
+        if (gate && *gate) return;
         if (kDir) beta = dir.st->beta;
     }
     const int lane = threadIdx.x & 63;
@@ -316,7 +317,6 @@ __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
         for (int e = 0; e < 3; ++e) asm volatile("" : "+v"(v[u][e].r), "+v"(v[u][e].i));
         if constexpr (kDir && !XPAY) pin(rn[u]);
     }
-    if (stop) return;
     if constexpr (kDir && !XPAY) {
         const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
         const StepEnd end(dir.st);
