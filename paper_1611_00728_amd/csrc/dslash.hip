@@ -427,16 +427,21 @@ void launch_g(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a
 }
 
 // Lanes per site of a launch: what the tuner found (or 1 for a configuration set by hand), else by
-// size.  Where the lines lie, us per launch one / four / eight lanes (18-real; 12-real alike):
+// size.  Where the lines lie, us per launch one / four / eight lanes (18-real, 12-real alike unless
+// named):
 //   eight: 8^4 FP64 10.6 / 4.6 / 3.7, FP32 7.4 / 3.9 / 3.3, FP16 10.1 / 3.7 / 3.5;
 //          12^4 FP64 19.3 / 6.0 / 6.2, FP32 13.0 / 4.9 / 5.1;
-//   four:  FP64 20^4 38.3 / 32.5, 24^4 68.9 / 72.7; FP32 20^4 18.8 / 15.1, 24^4 33.3 / 33.8;
-//          FP16 24^4 18.4 / 17.5 (12-real 22.5 / 16.7), 28^4 31.1 / 34.6.
-int split_of(const TuneEntry& t, int P, int vh)
+//   four:  FP64 20^4 38.3 / 32.5, 20x20x22x22 (96800 sites) 41.9 / 41.2, 20x22x22x22 43.3 / 46.3;
+//          FP32 20^4 18.8 / 15.1, 20x20x22x22 21.5 / 20.6, 22^4 (117128) 23.3 / 26.3, 12-real
+//          20x22x22x22 20.6 / 17.7, 22^4 21.2 / 23.0;
+//          FP16 24^3x26 (179712) 20.4 / 18.7, 24x24x26x26 21.2 / 22.5, 12-real 23.1 / 18.5.
+int split_of(const TuneEntry& t, int P, int RECON, int vh)
 {
     if (t.split > 0) return t.split;
     if (vh <= 4096) return 8;
-    return vh <= (P == KS_F64 ? 100000 : P == KS_F32 ? 130000 : 200000) ? 4 : 1;
+    const int most = RECON == 12 ? (P == KS_F64 ? 100000 : P == KS_F32 ? 110000 : 200000)
+                                 : (P == KS_F64 ? 100000 : P == KS_F32 ? 100000 : 185000);
+    return vh <= most ? 4 : 1;
 }
 
 // Dynamic LDS of a one-thread-per-site launch that nobody tuned: FP64 and FP32 run two blocks of 256 per
@@ -446,21 +451,26 @@ int split_of(const TuneEntry& t, int P, int vh)
 // 95.3 / 92.2 (90.6 / 83.5 / 79.5); 32^3x48 FP64 326 / 320 / 290, FP32 162 / 156 / 144; 48^3x32
 // FP64 732 / 724 / 691, FP32 366 / 360 / 338.  Where the last round of blocks would leave more than
 // 15 % of the chip's time empty, three: 28^4 (2.3 rounds of two) FP64 126 / 118 / 122, FP32 60.2 /
-// 57.5 / 61.1; 24^4 (1.3) 65.2 / 64.7 / 75.2.  FP16 has too few bytes per load for it: 32^4 52.1 /
-// 56.4 / 66.1.
+// 57.5 / 61.1; 24^4 (1.3) 65.2 / 64.7 / 75.2; but no request at all from 1.5 to 2 rounds, which
+// leave a second round of three nearly empty and are one of four: 24x26x26x26 (1.6) uncapped /
+// three FP64 87.1 / 89.7, FP32 45.1 / 47.5 (12-real 39.7 / 42.6).  FP16 has too few bytes per load
+// for it: 32^4 52.1 / 56.4 / 66.1.
 int lds_of(const TuneEntry& t, int P, int vh)
 {
     if (t.split > 0 || P == KS_F16) return t.lds;
     constexpr int kTwoPerCu = 80000, kThreePerCu = 52000;       // of 160 KB
     const double rounds = vh / (2.0 * 256 * 256);               // 256 CUs
-    return rounds >= 0.85 * std::ceil(rounds) ? kTwoPerCu : kThreePerCu;
+    if (rounds >= 0.85 * std::ceil(rounds)) return kTwoPerCu;
+    return rounds > 1.5 && rounds <= 2.0 ? 0 : kThreePerCu;
 }
 
-// Links of both parities up to this size are read through the caches: the last-level one (256 MB)
-// then still holds them, beside the vectors, at a solver's next step; larger ones are streamed.
-// CG step, streamed / through the caches: 186 MB (14x18x16x20 FP64) 48.7 / 43.0 us, 184 MB (20^4
-// FP32) 56.4 / 53.3, 133 MB (24^3x20 FP16 12-real) 56.5 / 52.8; 369 MB (20^4 FP64) 82.8 / 88.6.
-constexpr size_t kCachedLinks = (size_t)200 << 20;
+// Links of both parities up to this size are read through the caches: most of them then are still
+// in the last-level one (256 MB) at a solver's next step; larger ones are streamed.  CG, streamed /
+// through the caches: 186 MB (14x18x16x20 FP64) 48.7 / 43.0 us a step, 184 MB (20^4 FP32) 56.4 /
+// 53.3, 133 MB (24^3x20 FP16 12-real) 56.5 / 52.8; 225 MB (18^3x20 FP64 12-real) 14.8 / 13.4 ms a
+// solve, 225 MB (20x20x22x22 FP32) 16.5 / 15.2, 244 MB (18^4 FP64) 15.3 / 14.1, 251 MB
+// (18x18x20x20 FP64 12-real) 16.5 / 15.3; 369 MB (20^4 FP64) 82.8 / 88.6 us a step.
+constexpr size_t kCachedLinks = (size_t)260 << 20;
 
 template <int P, int RECON, int S, bool kStream, bool kDir>
 void launch_split(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a, hipStream_t s)
@@ -487,13 +497,18 @@ size_t link_bytes(int P, int RECON, int lp)
 
 // Where links stay in the caches a CG step is short, and the launch that writes its direction is a
 // good part of it (FP64 and FP32; a binary16 direction would have to be rounded to its record at
-// every neighbour).  CG step with / without that launch, us: FP64 8^4 14.8 / 12.8, 12^4 20.7 / 19.0, 16^4
-// 36.6 / 34.7, 14x18x16x20 (186 MB) 41.8 / 41.6, 18^4 (242 MB) 60.8 / 63.8; FP32 12^4 15.8 / 13.4, 16^4
-// 24.8 / 22.8, 20^4 (184 MB) 43.2 / 42.0, 20^3x24 (221 MB) 54.6 / 57.9, its 12-real form (184 MB)
-// 44.8 / 44.2.
+// every neighbour), up to a size at which the second vector that every neighbour then reads costs
+// more than that launch.  CG step with / without the launch, us: FP64 8^4 14.8 / 12.8, 12^4 20.7 /
+// 19.0, 16^4 36.6 / 34.7, 14x18x16x20 (186 MB) 41.8 / 41.6; FP32 12^4 15.8 / 13.4, 16^4 24.8 / 22.8,
+// 20^4 (184 MB) 43.2 / 42.0, its 12-real form at 20^3x24 (184 MB) 44.8 / 44.2.  Solve, ms: FP64
+// 18^3x20 (270 MB) 15.0 / 15.7, its 12-real form (225 MB) 13.0 / 13.4, 18x18x20x20 12-real (251 MB)
+// 14.6 / 15.3; FP32 20x20x22x22 (225 MB) 15.2 / 15.2.
+constexpr size_t kHandOnLinks = (size_t)200 << 20;
+
 bool forms_direction(const TuneEntry& t, int P, int RECON, const Geom& G)
 {
-    return P != KS_F16 && split_of(t, P, G.Vh) > 1 && link_bytes(P, RECON, G.lp) <= kCachedLinks;
+    return P != KS_F16 && split_of(t, P, RECON, G.Vh) > 1 &&
+           link_bytes(P, RECON, G.lp) <= kHandOnLinks;
 }
 
 template <int P, int RECON, int S>
@@ -544,7 +559,7 @@ template <int P, int RECON>
 void launch_p(const LinkStore& st, const Geom& G, double c0, const DslashArgs& a,
               TuneEntry t, hipStream_t s)
 {
-    const int split = split_of(t, P, G.Vh);
+    const int split = split_of(t, P, RECON, G.Vh);
     t.lds = lds_of(t, P, G.Vh);
     KS_REQUIRE(!a.dir || forms_direction(t, P, RECON, G), KS_ERR_ARG,
                "Dslash: this variant does not form the direction");
@@ -575,7 +590,7 @@ void launch(ks_gauge_t g, ks_prec_t prec, int ri, const DslashArgs& a, const Tun
 int dslash_blocks(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon)
 {
     const TuneEntry& t = g->tune[prec][recon_index(recon)];
-    const int split = split_of(t, (int)prec, g->geom.Vh);
+    const int split = split_of(t, (int)prec, (int)recon, g->geom.Vh);
     return blocks_for(g->geom.Vh, split > 1 ? kSplitThreads / split : t.nt);
 }
 

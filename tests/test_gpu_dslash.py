@@ -399,3 +399,62 @@ def test_calls_follow_the_current_stream(ks):
         assert seen == [torch.cuda.default_stream().cuda_stream]
         assert ks._stream(s.cuda_stream).value == s.cuda_stream
     assert now() == torch.cuda.current_stream().cuda_stream
+
+
+@pytest.mark.parametrize("dims,recon", [((22, 22, 22, 22), 18), ((22, 22, 22, 24), 18),
+                                        ((22, 22, 22, 22), 12)])
+def test_dslash_lanes_end_where_they_cost(ks, dims, recon):
+    """FP32 lattices just above the size up to which several lanes share a site: the untuned launch
+    is no more than 5 % slower than one thread per site (four lanes: 8-13 % slower)."""
+    import torch
+    announce("dslash lanes' upper end", dims, recon)
+    V = int(np.prod(dims))
+    g = make_gauge(dims, 0.5, 16)
+    G, H = ks.Gauge(dims, g.fat, g.naik), ks.Gauge(dims, g.fat, g.naik)
+    H.set_config(ks.F32, recon, lds_bytes=16)
+    best = {}
+    psi = dev(gaussian_source(V // 2, 43))
+    fields = {L: (ks.Field(L, 0, ks.F32).load(psi), ks.Field(L, 1, ks.F32), ks.Field(L, 0, ks.F32))
+              for L in (G, H)}
+    for _ in range(12):
+        for L, (x, y, z) in fields.items():
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            for k in range(42):
+                if k == 2:
+                    e[0].record()
+                ks.dslash_eo(L, y, x, recon)
+                ks.dslash_eo(L, z, y, recon)
+            e[1].record()
+            torch.cuda.synchronize()
+            best[L] = min(best.get(L, 1e9), e[0].elapsed_time(e[1]))
+    assert best[G] <= 1.05 * best[H]
+
+
+# several lanes per site with links past the size up to which they are read through the caches:
+# FP64 by size (64152 and 79200 sites per parity), FP32 and FP16 where a tuning file asks for it
+@pytest.mark.parametrize("dims,prec,recon,lanes", [
+    ((18, 18, 18, 22), "f64", 18, None), ((18, 20, 20, 22), "f64", 12, None),
+    ((22, 22, 22, 24), "f32", 18, 4), ((24, 24, 24, 24), "f32", 12, 8),
+    ((26, 26, 26, 28), "f16", 18, 8), ((28, 28, 28, 28), "f16", 12, 4)])
+def test_dslash_lanes_with_streamed_links(ks, tmp_path, monkeypatch, dims, prec, recon, lanes):
+    import json
+    announce("dslash lanes, streamed links", dims, prec, recon, lanes)
+    g = make_gauge(dims, 0.5, 14)
+    G = ks.Gauge(dims, g.fat, g.naik)
+    vh = g.volume // 2
+    P = ks.PREC[prec]
+    if lanes:
+        path = tmp_path / "tune.jsonl"
+        monkeypatch.setenv("KS_TUNE_CACHE", str(path))
+        s = make_gauge((4, 4, 4, 4), 0.5, 15)
+        ks.Gauge(s.dims, s.fat, s.naik).tune(P, recon)
+        e = json.loads(path.read_text())
+        e.update(dims=list(dims), threads=256, lds_bytes=0, links_per_pass=1, link_access=8,
+                 staged=0, us=2.5, split=lanes)
+        path.write_text(json.dumps(e) + "\n")
+        assert G.tune(P, recon)["tuned_us"] == pytest.approx(2.5)
+    for out_par in (0, 1):
+        psi = gaussian_source(vh, 520 + out_par)
+        got = run_dslash(ks, G, vh, out_par, psi, P, recon)
+        ref, S = dc.reference(g, prec, recon, 8, out_par, psi)
+        assert dc.worst(got, ref, S, prec) <= 1.0

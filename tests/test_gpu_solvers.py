@@ -477,3 +477,27 @@ def test_stopped_steps_read_no_links(ks):
     stopped, n_stopped = seconds(1e-3, 10.0)
     assert n_live == 400 and n_stopped <= 40
     assert stopped <= 0.5 * live
+
+
+# 64152 sites: links past the size up to which they are read through the caches
+def test_cg_with_streamed_links_and_lanes(ks):
+    """Steps whose links stream from memory do not hand their directions on: a solve that reads
+    its state after every step and one that reads it after several return the same bits."""
+    import torch
+    announce("cg streamed lanes")
+    dims = (18, 18, 18, 22)
+    V = int(np.prod(dims))
+    gen = torch.Generator(device="cuda").manual_seed(10)
+    links = [0.2 * torch.randn(4, V, 3, 3, generator=gen, dtype=torch.complex128, device="cuda")
+             for _ in range(2)]
+    G = ks.Gauge(dims, *links)
+    b = dev(gaussian_source(V // 2, 94))
+    runs = []
+    for every in (1, 16):
+        x = zeros_dev((V // 2, 3))
+        r = ks.cg_solve(G, 0.05, b, x, ks.default_params(tol=1e-30, max_iter=40, check_every=every,
+                                                        max_restarts=0), raise_on_error=False)
+        torch.cuda.synchronize()
+        runs.append((r.stats["iters"], host(x)))
+    assert runs[0][0] == runs[1][0] == 40
+    assert np.all(np.isfinite(runs[0][1])) and np.array_equal(runs[0][1], runs[1][1])
