@@ -680,7 +680,7 @@ def main():
                     best = None
                     for group in (1, 2, 4):
                         for nt in (64, 128, 256):
-                            for lds in (0, 13312, 20224, 32512, 54272):
+                            for lds in (16, 13312, 20224, 32512, 54272):   # 16: no cap
                                 try:
                                     G.set_config(pmap[v[0]], v[1], nt, lds, group, way, staged)
                                 except ks.KSError:

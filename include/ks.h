@@ -151,9 +151,10 @@ ks_status_t ks_dslash_eo(ks_gauge_t g, ks_field_t out, ks_field_t in, ks_recon_t
 /* Autotuner: times the Dslash of precision `prec` / Naik storage `recon` on this lattice
  * over candidate launch configurations (64, 128 or 256 threads per block; blocks per CU
  * capped through the LDS request) and keeps the fastest for every later launch through this
- * handle (ks_dslash_eo and the solvers).  Untuned variants use 256 threads and no cap, on small
- * lattices with four or eight lanes per output site (a form that the tuner also times and that
- * has no field in ks_dslash_launch; a configuration set by hand has one thread per site).  Allocates
+ * handle (ks_dslash_eo and the solvers).  It also times forms with four or eight lanes per output
+ * site.  Untuned variants take the form that the lattice's size suggests: four or eight lanes
+ * per site on small lattices, else 256 threads with one site each, in FP64 and FP32 with an LDS
+ * request that lets two or three blocks share a CU where that fills the chip evenly.  Allocates
  * two scratch fields for the duration of the call; synchronises the stream.  Must not be
  * called while the stream is being captured into a graph.
  * With the environment variable KS_TUNE_CACHE naming a file, the configuration is taken from
@@ -165,7 +166,8 @@ ks_status_t ks_dslash_eo(ks_gauge_t g, ks_field_t out, ks_field_t in, ks_recon_t
 ks_status_t ks_tune_dslash(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t stream);
 
 /* Launch configuration of one Dslash variant:
- *   threads         64, 128 or 256 threads per block (one output site per thread);
+ *   threads         64, 128 or 256 threads per block (one output site per thread, but for the
+ *                   default values);
  *   lds_bytes       dynamic LDS requested per block (0 to the device's LDS per workgroup);
  *                   it caps how many blocks share a CU, and the staged form uses at least
  *                   what its staging needs;
@@ -180,7 +182,11 @@ ks_status_t ks_tune_dslash(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipSt
  *                   block's x and y neighbourhood are first staged in LDS by one coalesced read
  *                   and those gathers read LDS;
  *   tuned_us        time per launch measured by the autotuner (0 if never tuned; ignored by
- *                   ks_dslash_set_config). */
+ *                   ks_dslash_set_config).
+ * The default values {256, 0, 1, 8, 0} stand for the lanes per site that the autotuner found on
+ * this handle, where it found several, else for the untuned form (see ks_tune_dslash); so a
+ * configuration read from a handle and set on it again is the same launch.  256 threads with one
+ * site each and no cap are {256, 16, 1, 8, 0}: a request too small to keep a block off a CU. */
 typedef struct {
     int threads;
     int lds_bytes;

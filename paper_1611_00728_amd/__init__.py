@@ -213,7 +213,8 @@ class Gauge:
 
     def set_config(self, prec=F64, recon=RECON_18, threads=256, lds_bytes=0,
                    links_per_pass=1, link_access=8, staged=0):
-        """Sets one variant's Dslash launch configuration by hand."""
+        """Sets one variant's Dslash launch configuration by hand; the defaults restore the lanes
+        per site that tune found, else the untuned form."""
         cfg = DslashLaunch(threads, lds_bytes, links_per_pass, link_access, staged, 0.0)
         _check(lib().ks_dslash_set_config(self.handle, prec, recon, C.byref(cfg)))
 

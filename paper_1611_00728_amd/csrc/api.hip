@@ -351,8 +351,10 @@ ks_status_t ks_dslash_set_config(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon,
     t.group = cfg->links_per_pass;
     t.way = cfg->link_access;
     t.staged = cfg->staged;
-    t.split = 1;
-    g->tune[prec][recon_index(recon)] = t;
+    TuneEntry& now = g->tune[prec][recon_index(recon)];
+    t.found = now.found;
+    t.split = t.is_default() ? t.found : 1;
+    now = t;
     return KS_SUCCESS;
     KS_API_END
 }

@@ -31,6 +31,9 @@ namespace ks {
 namespace {
 
 constexpr int kSplitThreads = 256;   // threads per block of the split form
+// LDS request of an uncapped one-thread-per-site launch whose other values are the default ones
+// (no request stands for the form chosen by size)
+constexpr int kUncapped = 16;
 
 template <class R>
 __device__ __forceinline__ void matvec_acc(cx<R> acc[3], const cx<R> m[9], const cx<R> v[3])
@@ -682,6 +685,7 @@ bool parse_line(const std::string& line, CacheKey& k, TuneEntry& t)
     if (n == 14 || t.way != 8 || t.staged || t.group != 1 || t.nt != kSplitThreads || t.lds != 0 ||
         (t.split != 4 && t.split != 8))
         t.split = 1;
+    if (t.split == 1 && t.is_default()) t.lds = kUncapped;
     k.arch = arch;
     t.us = us;
     return true;
@@ -778,6 +782,7 @@ void dslash_tune(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t s)
                 G.n[2], G.n[3]);
         if (usable) {
             t.tuned = true;
+            t.found = t.split > 1 ? t.split : 0;
             g->tune[prec][ri] = t;
             return;
         }
@@ -821,6 +826,8 @@ void dslash_tune(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t s)
                     l -= l % 256;
                     if (l <= 0 || l > lds_blk) continue;
                     t.lds = (int)l;
+                } else if (t.is_default()) {
+                    t.lds = kUncapped;
                 }
                 for (int k = 0; k < 2; ++k) launch(g, prec, ri, a, t, s);
                 timed.push_back({time_launches(g, prec, ri, a, t, 5, e0, e1, s), t});
@@ -857,6 +864,7 @@ void dslash_tune(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t s)
     device_free(out);
     best.us = best_us;
     best.tuned = true;
+    best.found = best.split > 1 ? best.split : 0;
     g->tune[prec][ri] = best;
     log_msg(1, "tuned %s %d-real Dslash at %dx%dx%dx%d: %d threads, %d links per pass, %d-way, "
                "%s gathers, %d B LDS, %d lanes per site, %.1f us",

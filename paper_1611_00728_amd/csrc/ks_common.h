@@ -93,9 +93,12 @@ struct TuneEntry {
     int way = 8;        // 8: a site's own backward slots; 4: neighbours' forward slots
     int staged = 0;     // 1: x/y neighbour vectors staged in LDS
     int split = 0;      // lanes per site; 0: by the lattice's size
+    int found = 0;      // lanes per site that the tuner found on this handle (0: not tuned, or one)
     int lds = 0;
     float us = 0.f;     // measured time per launch when tuned
     bool tuned = false;
+    // the values that stand for a form of several lanes per site or the one chosen by size
+    bool is_default() const { return nt == 256 && group == 1 && way == 8 && !staged && lds == 0; }
 };
 
 }  // namespace ks

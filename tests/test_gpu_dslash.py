@@ -401,6 +401,62 @@ def test_calls_follow_the_current_stream(ks):
     assert now() == torch.cuda.current_stream().cuda_stream
 
 
+def test_config_read_and_set_again_is_the_same_launch(ks, tmp_path, monkeypatch):
+    """A configuration that a handle reports and takes back gives the launch it reported, bit for
+    bit (one, four and eight lanes per site add in different orders): untuned, tuned to other
+    lanes than the size suggests, and tuned to one thread per site; the default values restore
+    the untuned form."""
+    import json
+    announce("config read and set again")
+    path = tmp_path / "tune.jsonl"
+    monkeypatch.setenv("KS_TUNE_CACHE", str(path))
+    dims = (8, 8, 8, 8)
+    g = make_gauge(dims, 0.5, 3)
+    vh = g.volume // 2
+    psi = gaussian_source(vh, 811)
+    ks.Gauge(dims, g.fat, g.naik).tune(ks.F64, 18)
+    e = json.loads(path.read_text())
+    e.update(threads=256, lds_bytes=0, links_per_pass=1, link_access=8, staged=0, us=1.5)
+    outs = {}
+    for split in (None, 4, 1):
+        G = ks.Gauge(dims, g.fat, g.naik)
+        if split:
+            path.write_text(json.dumps(dict(e, split=split)) + "\n")
+            G.tune(ks.F64, 18)
+        outs[split] = run_dslash(ks, G, vh, 1, psi, ks.F64, 18)
+        cfg = G.config(ks.F64, 18)
+        cfg.pop("tuned_us")
+        G.set_config(ks.F64, 18, threads=64)
+        outs["hand"] = run_dslash(ks, G, vh, 1, psi, ks.F64, 18)
+        assert np.array_equal(outs["hand"], outs[split]) == (split == 1)
+        G.set_config(ks.F64, 18, **cfg)
+        assert np.array_equal(run_dslash(ks, G, vh, 1, psi, ks.F64, 18), outs[split])
+        if split is None:
+            G.set_config(ks.F64, 18, threads=64)
+            G.set_config(ks.F64, 18)
+            assert np.array_equal(run_dslash(ks, G, vh, 1, psi, ks.F64, 18), outs[None])
+    assert not np.array_equal(outs[4], outs[None])
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_dslash_blocks_per_cu_changes_no_bit(ks, prec):
+    """Two (256000 sites), three (160000) and four (202400, where a second round of three would
+    be nearly empty) blocks per CU against the same form uncapped."""
+    import torch
+    for dims in ((20, 20, 20, 64), (20, 20, 20, 40), (20, 20, 22, 46)):
+        announce("dslash blocks per CU, uncapped", dims, prec)
+        V = int(np.prod(dims))
+        gen = torch.Generator(device="cuda").manual_seed(8)
+        fat, naik = (torch.randn(4, V, 3, 3, generator=gen, dtype=torch.complex128, device="cuda")
+                     for _ in range(2))
+        G, H = ks.Gauge(dims, fat, naik), ks.Gauge(dims, fat, naik)
+        H.set_config(ks.PREC[prec], 18, lds_bytes=16)
+        psi = gaussian_source(V // 2, 42)
+        outs = [run_dslash(ks, L, V // 2, 1, psi, ks.PREC[prec], 18) for L in (G, H)]
+        assert np.abs(outs[1]).max() > 0
+        assert np.array_equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("dims,recon", [((22, 22, 22, 22), 18), ((22, 22, 22, 24), 18),
                                         ((22, 22, 22, 22), 12)])
 def test_dslash_lanes_end_where_they_cost(ks, dims, recon):
