@@ -202,6 +202,15 @@ __device__ __forceinline__ void hop_site_f16(const LatDesc& L, int h, const int 
     }
 }
 
+// Place of the partial sums of the tile that starts at site h0: a lattice's tiles in the order of
+// their sites, whatever place the tile has in the table.  The tables' order depends on how many
+// tiles the lattices before it have; the sums of a lattice, and so its solution, do not.
+template <int NT>
+__device__ __forceinline__ size_t part_slot(const LatDesc& L, int h0)
+{
+    return (size_t)(L.tile_begin + h0 / NT);
+}
+
 // res_r = (D in_r)(h) for the R right-hand sides of site h, links and vectors of precision PP.
 // Hops per pass of the 16: FP32 keeps four link and neighbour loads in flight
 // (measured best; a full unroll is slower); FP64 at four hops would spill.
@@ -272,7 +281,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void ba
         const int mode = lattice_mode(pairs, L.pair0, R);
         if (XPAY && tl.y == 0 && threadIdx.x == 0) pairs[L.pair0].s_mode = mode;
         if (mode == 0) {
-            if (XPAY && threadIdx.x < R) partials[(size_t)t * R + threadIdx.x] = 0.0;
+            if (XPAY && threadIdx.x < R) partials[part_slot<NT>(L, tl.y) * R + threadIdx.x] = 0.0;
             continue;
         }
         const int vh = L.g.Vh;
@@ -325,14 +334,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void ba
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const double s = block_sum<NT>(dot[r]);
-                if (threadIdx.x == 0) partials[(size_t)t * R + r] = s;
+                if (threadIdx.x == 0) partials[part_slot<NT>(L, tl.y) * R + r] = s;
                 __syncthreads();
             }
         }
     }
 }
 
-// Sums over the lattice's tiles of the partials of every RHS (thread j adds tiles j, j + NT,
+// Sums over the lattice's tiles of the partials of every RHS (thread j adds slots j, j + NT,
 // ... in order, then the fixed wave and block order): every block of the lattice gets the
 // same totals bit for bit.
 template <int NT, int R>
@@ -470,7 +479,7 @@ __global__ __launch_bounds__(NT) void batch_update_kernel(
 #pragma unroll
             for (int k = 0; k < R; ++k) {
                 const double s = block_sum<NT>(nrm[k]);
-                if (threadIdx.x == 0) part2[(size_t)t * R + k] = s;
+                if (threadIdx.x == 0) part2[part_slot<NT>(L, tl.y) * R + k] = s;
                 __syncthreads();
             }
         } else {
@@ -687,7 +696,7 @@ __global__ __launch_bounds__(NT) void batch_flush_kernel(const LatDesc* __restri
     }
 }
 
-// One block per pair: its lattice's tile partials in tile order.
+// One block per pair: its lattice's tile partials in slot order.
 __device__ __forceinline__ double pair_sum(const LatDesc& L, const double* part, int R, int r)
 {
     double s = 0.0;
@@ -735,12 +744,12 @@ __global__ __launch_bounds__(NT) void batch_b2_kernel(const LatDesc* __restrict_
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const double s = block_sum<NT>(nrm[k]);
-        if (threadIdx.x == 0) partials[(size_t)t * R + k] = s;
+        if (threadIdx.x == 0) partials[part_slot<NT>(L, tl.y) * R + k] = s;
         __syncthreads();
     }
 }
 
-// Per pair: |b|^2 (the tile partials in tile order) and the initial scalars (one block per pair).
+// Per pair: |b|^2 (the tile partials in slot order) and the initial scalars (one block per pair).
 __global__ __launch_bounds__(kFin) void batch_init_pairs_kernel(const LatDesc* __restrict__ lats,
                                                                 int R, BatchPair* __restrict__ pairs,
                                                                 const double* __restrict__ part,

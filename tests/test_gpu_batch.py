@@ -180,3 +180,28 @@ def test_batch_tile_order(ks, dims, nrhs, inner):
     for p, (b, x) in enumerate(zip(bh, xh)):
         assert true_rel(gs[p // nrhs], 4 * masses[p // nrhs] ** 2, b, x) <= 1e-10
     B.free()
+
+
+@pytest.mark.parametrize("inner", ["f64", "f32", "f16"])
+def test_batch_lattice_does_not_depend_on_its_place(ks, inner):
+    """The sums of a lattice run over its tiles in the order of their sites: its solutions are
+    the same bits alone and behind lattices of 2 + 3 tiles."""
+    import torch
+    announce("batch place", inner)
+    gs = [make_gauge(d, 0.4, 4600 + j) for j, d in enumerate([(4, 4, 4, 4), (6, 4, 4, 4), (8, 8, 8, 8)])]
+    b = [[gaussian_source(g.volume // 2, 4610 + 2 * j + r) for r in range(2)] for j, g in enumerate(gs)]
+    mass = [0.2, 0.3, 0.1]
+    runs = []
+    for pick in ([2], [0, 1, 2]):
+        B = ks.Batch([gs[j].dims for j in pick], [gs[j].fat for j in pick],
+                     [gs[j].naik for j in pick], 2, ks.PREC[inner])
+        xs = [zeros_dev(v.shape) for j in pick for v in b[j]]
+        rc, st = B.solve([mass[j] for j in pick], [dev(v) for j in pick for v in b[j]], xs,
+                         ks.default_params(tol=1e-10, check_every=4))
+        torch.cuda.synchronize()
+        assert rc == 0
+        runs.append(([s["iters"] for s in st[-2:]], [host(x) for x in xs[-2:]]))
+        B.free()
+    assert runs[0][0] == runs[1][0]
+    for x, y in zip(runs[0][1], runs[1][1]):
+        assert np.array_equal(x, y)
