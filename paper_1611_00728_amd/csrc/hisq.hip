@@ -542,29 +542,31 @@ constexpr size_t kWideScratch = (size_t)32 << 30;
 struct HisqScratch {
     void* ptr = nullptr;
     size_t bytes = 0;
-    size_t no_more = ~(size_t)0;   // a size that the device could not give
 };
 std::mutex g_hisq_mu;
 std::map<int, HisqScratch> g_hisq;
 
-// `bytes` of scratch, or `fewer` if the device cannot give that many; *got says which
+// `bytes` of scratch, or `fewer` if the device cannot give that many; *got says which.  A call that
+// finds `fewer` from an earlier shortage moves to `bytes` as soon as the device has them free
+// (beside what is held, so that a failed try gives nothing up).
 char* hisq_scratch(size_t bytes, size_t fewer, size_t* got)
 {
     int dev = 0;
     KS_HIP(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(g_hisq_mu);
     HisqScratch& h = g_hisq[dev];
-    if (h.bytes < bytes && !(h.bytes >= fewer && h.no_more <= bytes)) {
+    auto take = [&](void* p, size_t n) {
         device_free(h.ptr);
-        h.ptr = nullptr;
-        h.bytes = 0;
+        h.ptr = p;
+        h.bytes = n;
+    };
+    if (h.bytes < fewer) take(nullptr, 0);
+    size_t room = 0, total = 0;
+    if (h.bytes < bytes && (h.bytes == 0 || (hipMemGetInfo(&room, &total) == hipSuccess && room >= bytes))) {
         try {
-            h.ptr = device_alloc(bytes);
-            h.bytes = bytes;
+            take(device_alloc(bytes), bytes);
         } catch (const Failure&) {
-            h.ptr = device_alloc(fewer);
-            h.bytes = fewer;
-            h.no_more = bytes;
+            if (h.bytes == 0) take(device_alloc(fewer), fewer);
         }
     }
     *got = h.bytes >= bytes ? bytes : fewer;

@@ -150,3 +150,35 @@ def test_hisq_one_direction_per_pass(ks, dims):
     torch.cuda.empty_cache()
     assert left >= 5 * field        # the 32 fields were not there to take
     assert torch.equal(fat, fat2) and torch.equal(naik, naik2)
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 16, 16), (14, 10, 18, 16)])
+def test_hisq_takes_the_wide_scratch_once_it_fits(ks, dims):
+    """A call that finds room for 14 scratch fields only takes those, forms the same bits, and does
+    not decide for later calls: with memory free again the next one holds 32."""
+    import torch
+    announce("hisq scratch after a shortage", dims)
+    thin = dev(thin_links(dims, 0.5, 127).reshape(-1))
+    out = [torch.empty_like(thin) for _ in range(4)]
+    field = int(np.prod(dims)) * 144
+    free = lambda: torch.cuda.mem_get_info()[0]
+    ks.hisq_release()
+    torch.cuda.empty_cache()
+    filler = []
+    while free() > 30 * field:         # one block may leave more than asked for
+        filler.append(torch.empty(free() - 25 * field, dtype=torch.uint8, device="cuda"))
+    held = [free()]
+    ks.hisq_links(dims, thin, out[0], out[1])
+    torch.cuda.synchronize()
+    held.append(free())
+    del filler
+    torch.cuda.empty_cache()
+    held.append(free())
+    ks.hisq_links(dims, thin, out[2], out[3])
+    torch.cuda.synchronize()
+    held.append(free())
+    ks.hisq_release()
+    announce([round(h / field, 1) for h in held])
+    assert 13 * field <= held[0] - held[1] <= 20 * field
+    assert held[2] - held[3] >= 14 * field
+    assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
