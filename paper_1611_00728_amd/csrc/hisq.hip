@@ -122,7 +122,10 @@ __device__ __forceinline__ void axpy_mat(Mat& acc, double w, const Mat& m)
     }
 }
 
-// acc += w a m b^+ (the staple of the middle link m in a positive direction)
+// acc += w a m b^+ (the staple of the middle link m in a positive direction).  The staple is summed
+// up by itself and rounded into acc once: acc is several times its size, and six products per real
+// entry added to acc one by one round at that size six times (level 2 alone, random links: relative
+// error 2.8e-16, 1.3e-16 this way; both smearings at 32^4 7.41 and 7.43 ms).
 __device__ __forceinline__ void staple_fwd(Mat& acc, const Mat& a, const Mat& m, const Mat& b,
                                            double w = 1.0)
 {
@@ -137,14 +140,17 @@ __device__ __forceinline__ void staple_fwd(Mat& acc, const Mat& a, const Mat& m,
             t[j] = {w * t[j].r, w * t[j].i};
         }
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
+        for (int j = 0; j < 3; ++j) {
+            cxd s = {0.0, 0.0};
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
                 const cxd y = b.e[j * 3 + k];
-                cxd& s = acc.e[i * 3 + j];
                 s.r = fma(t[k].r, y.r, fma(t[k].i, y.i, s.r));
                 s.i = fma(t[k].i, y.r, fma(-t[k].r, y.i, s.i));
             }
+            acc.e[i * 3 + j].r += s.r;
+            acc.e[i * 3 + j].i += s.i;
+        }
     }
 }
 
@@ -167,9 +173,13 @@ __device__ __forceinline__ void staple_bwd(Mat& acc, const Mat& a, const Mat& m,
             t[j] = {w * t[j].r, w * t[j].i};
         }
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
+        for (int j = 0; j < 3; ++j) {
+            cxd s = {0.0, 0.0};
 #pragma unroll
-            for (int k = 0; k < 3; ++k) cfma(acc.e[i * 3 + j], t[k], b.e[k * 3 + j]);
+            for (int k = 0; k < 3; ++k) cfma(s, t[k], b.e[k * 3 + j]);
+            acc.e[i * 3 + j].r += s.r;
+            acc.e[i * 3 + j].i += s.i;
+        }
     }
 }
 

@@ -182,3 +182,24 @@ def test_hisq_takes_the_wide_scratch_once_it_fits(ks, dims):
     assert 13 * field <= held[0] - held[1] <= 20 * field
     assert held[2] - held[3] >= 14 * field
     assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
+
+
+@pytest.mark.parametrize("scale", [0.5, 5.0])
+def test_hisq_smearing_rounds_each_staple_once(ks, scale):
+    """The level-2 smearing of the very links W that the device projects to, against extended
+    precision: F is a sum of seven terms, the largest about |F| and the others a fifth of it, so
+    six roundings of at most u / sqrt(3) rms of |F| (u = 2^-53) and, of each staple, some twelve
+    of a fifth of that: sqrt(6) (1 + 0.2^2 12)^(1/2) u / sqrt(3) = 1.9e-16.  Products added to F one
+    by one would round 36 times (measured 2.4e-16)."""
+    announce("hisq smearing rounding", scale)
+    dims = (6, 6, 6, 6)
+    U = thin_links(dims, scale, 128)
+    one = (1.0, 0.0, 0.0, 0.0, 0.0)
+    W, _ = build(ks, dims, U, one, one)
+    F, _ = build(ks, dims, U, one)
+    W, _ = hisq.fold_signs(W, W, dims)                   # the signs taken out again
+    ref = hisq.smear(W.astype(np.clongdouble), dims, hisq.LEVEL2)
+    ref, _ = hisq.fold_signs(ref, ref, dims)
+    rms = lambda a: float(np.sqrt(np.mean(np.abs(a) ** 2)))
+    print("[gpu case] relative rms error %.3e" % (rms(F - ref) / rms(ref)), flush=True)
+    assert rms(F - ref) <= 1.9e-16 * rms(ref)
