@@ -80,6 +80,8 @@ dslash_multi_kernel(Geom g, int par, const void* __restrict__ fat, const void* _
                     TermVecs in, TermVecs out, int first, int last, float fat_scale,
                     float naik_scale)
 {
+    extern __shared__ double2 one_link[];   // kMultiLds bytes: a thread's own 3 K entries
+    static_assert(3 * K * kBlock * sizeof(double2) <= kMultiLds, "one_link");
     const int vh = g.Vh;
     const int wave = xcd_tile(blockIdx.x, gridDim.x) * (kBlock / 64) + (threadIdx.x >> 6);
     const int hh = wave * kSites + threadIdx.x % kSites;
@@ -118,6 +120,27 @@ dslash_multi_kernel(Geom g, int par, const void* __restrict__ fat, const void* _
                 res[q][a].i = fma(sc, u.i, res[q][a].i);
             }
         }
+        if (kGroups == 2 && u == 7) {
+            // the one-link sums wait in LDS, so that the Naik ones start from zero: eight additions
+            // to each, as with one group, and the same bits
+#pragma unroll
+            for (int q = 0; q < K; ++q)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    one_link[(q * 3 + a) * kBlock + threadIdx.x] = make_double2(res[q][a].r, res[q][a].i);
+                    res[q][a] = {0.0, 0.0};
+                }
+        }
+    }
+    if constexpr (kGroups == 2) {
+#pragma unroll
+        for (int q = 0; q < K; ++q)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double2 f = one_link[(q * 3 + a) * kBlock + threadIdx.x];
+                res[q][a].r += f.x;
+                res[q][a].i += f.y;
+            }
     }
     if constexpr (kGroups == 1) {
 #pragma unroll

@@ -105,3 +105,23 @@ def test_force_terms_per_pass(ks, dims, nterm):
         ov, ow = oracle.force_outer(g, res, xs[:n])
         for got, ref in ((host(fv).reshape(ov.shape), ov), (host(fw).reshape(ow.shape), ow)):
             assert np.max(np.abs(got - ref)) <= 1e-12 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 8, 8), (6, 10, 10, 4)])
+def test_force_is_the_same_in_any_pass(ks, dims):
+    """A solution's odd image is summed up in one order however many terms share the pass over the
+    links: with all other residues zero every number of terms gives the force of one term."""
+    announce("force bits", dims)
+    import torch
+    g = make_gauge(dims, 0.5, 99)
+    G = ks.Gauge(dims, g.fat, g.naik)
+    xs = [dev(gaussian_source(g.volume // 2, 120 + i)) for i in range(11)]
+    outs = []
+    for n in (1, 5, 6, 10, 11):
+        fv = torch.zeros(4 * g.volume * 9, dtype=torch.complex128, device="cuda")
+        fw = torch.zeros_like(fv)
+        ks.force(G, [0.7] + [0.0] * (n - 1), xs[:n], fv, fw)
+        torch.cuda.synchronize()
+        outs.append((host(fv), host(fw)))
+    for fv, fw in outs[1:]:
+        assert np.array_equal(fv, outs[0][0]) and np.array_equal(fw, outs[0][1])
