@@ -219,7 +219,7 @@ void gauge_prepare(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t s
 
     // fat planes: shared between the 18- and 12-real stores of one precision
     LinkStore& base = g->store[prec][0];
-    if (!base.fat[0]) {
+    if (!base.fat[1]) {
         double fs = 1.0;
         if (prec == KS_F16) {
             double mx = 0.0;
@@ -227,7 +227,7 @@ void gauge_prepare(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t s
                 mx = fmax(mx, device_absmax(static_cast<const double*>(m.fat[par]), 2 * n18, s));
             fs = frexp_scale(mx);
         }
-        for (int par = 0; par < 2; ++par) {
+        for (int par = base.fat[0] ? 1 : 0; par < 2; ++par) {
             base.fat[par] = device_alloc_zero(n18 * entry_bytes(prec), s);
             base.bytes += n18 * entry_bytes(prec);
             pack<9>(prec, static_cast<const double2*>(m.fat[par]), base.fat[par], G, fs, s);
@@ -253,6 +253,7 @@ void gauge_prepare(ks_gauge_t g, ks_prec_t prec, ks_recon_t recon, hipStream_t s
                 st.naik[par] = m.naik[par];
                 continue;
             }
+            if (st.naik[par]) continue;   // from a call that found no room for the other
             st.naik[par] = device_alloc_zero(n18 * entry_bytes(prec), s);
             st.bytes += n18 * entry_bytes(prec);
             pack<9>(prec, static_cast<const double2*>(m.naik[par]), st.naik[par], G, ns, s);

@@ -48,6 +48,16 @@ void* device_alloc(size_t bytes);
 // device_alloc, then the memory cleared on stream s (link stores: their padding rows are zero)
 void* device_alloc_zero(size_t bytes, hipStream_t s);
 void device_free(void* p);
+// p's memory if it has none yet.  Buffers that a handle keeps are taken one by one this way, so that a
+// call which finds no room for all of them leaves nothing that a later one would take for whole.
+// Returns the bytes it added.
+template <class T>
+inline size_t alloc_once(T*& p, size_t bytes)
+{
+    if (p) return 0;
+    p = static_cast<T*>(device_alloc(bytes));
+    return bytes;
+}
 
 // ------------------------------------------------------------------ geometry
 

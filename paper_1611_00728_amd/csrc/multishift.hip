@@ -336,24 +336,19 @@ ks_status_t multishift_core(ks_gauge_t g, int nshift, const double* sigma, const
     if (w.ms_prec != (int)P) {
         for (void* v : w.ms_p) device_free(v);
         w.ms_p.clear();
-        device_free(w.ms_r);
-        device_free(w.ms_pb);
-        device_free(w.ms_q);
-        device_free(w.ms_t);
-        w.ms_r = device_alloc(fb);
-        w.ms_pb = device_alloc(fb);
-        w.ms_q = device_alloc(fb);
-        w.ms_t = device_alloc(fb);
+        for (void** v : {&w.ms_r, &w.ms_pb, &w.ms_q, &w.ms_t}) {
+            device_free(*v);
+            *v = nullptr;
+        }
         w.ms_prec = (int)P;
     }
+    for (void** v : {&w.ms_r, &w.ms_pb, &w.ms_q, &w.ms_t}) alloc_once(*v, fb);
     while ((int)w.ms_p.size() < nshift) w.ms_p.push_back(device_alloc(fb));
     const bool sloppy = P != KS_F64;
     if (sloppy)
         while ((int)w.ms_dx.size() < nshift) w.ms_dx.push_back(device_alloc(field_bytes(G, KS_F32)));
-    if (!w.ms_st) {
-        w.ms_st = device_alloc(sizeof(MSState));
-        KS_HIP(hipHostMalloc(&w.ms_st_host, sizeof(MSState)));
-    }
+    alloc_once(w.ms_st, sizeof(MSState));
+    if (!w.ms_st_host) KS_HIP(hipHostMalloc(&w.ms_st_host, sizeof(MSState)));
     MSState* st = static_cast<MSState*>(w.ms_st);
     MSState* hs = static_cast<MSState*>(w.ms_st_host);
 

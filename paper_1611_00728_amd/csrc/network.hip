@@ -867,12 +867,12 @@ size_t layer_weight_offset(int l)
 NetBuffers& net_buffers(NetCtx& n, const Geom& g)
 {
     NetBuffers& B = n.bufs[g.Vh];
-    if (!B.act[0]) {
+    if (B.vh == 0) {
         const size_t site = (size_t)2 * 3 * g.Vh * sizeof(float2);   // one channel, both parities
         const int ch[5] = {1, 8, 8, 8, 1};
         for (int l = 0; l < 5; ++l) {
-            if (l < 4) B.act[l] = static_cast<float2*>(device_alloc(site * ch[l]));
-            B.grad[l] = static_cast<float2*>(device_alloc(site * ch[l]));
+            if (l < 4) alloc_once(B.act[l], site * ch[l]);
+            alloc_once(B.grad[l], site * ch[l]);
         }
         B.vh = g.Vh;
     }

@@ -376,10 +376,7 @@ void apply_layers(NetCtx& n, ks_gauge_t g, const void* r, void* z, const double*
                   const int* gate, hipStream_t s)
 {
     NetBuffers& B = net_buffers(n, g->geom);
-    if (!B.act16[1]) {
-        const size_t bytes = (size_t)2 * 6 * 16 * g->geom.Vh;
-        for (int l = 1; l <= 3; ++l) B.act16[l] = static_cast<__half*>(device_alloc(bytes));
-    }
+    for (int l = 1; l <= 3; ++l) alloc_once(B.act16[l], (size_t)2 * 6 * 16 * g->geom.Vh);
     const half4_t* fr = reinterpret_cast<const half4_t*>(n.wmma);
     constexpr int F = kFrags * 64;
     launch_layer<1, 8, V, void>(g, r, B.act16[1], fr, scale, gate, s);

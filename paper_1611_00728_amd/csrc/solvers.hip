@@ -23,10 +23,7 @@ size_t spinor_bytes(ks_prec_t p) { return p == KS_F64 ? 48 : p == KS_F32 ? 24 : 
 template <class T>
 T* ws_vec(Workspace& w, T*& slot, size_t bytes)
 {
-    if (!slot) {
-        slot = static_cast<T*>(device_alloc(bytes));
-        w.bytes += bytes;
-    }
+    w.bytes += alloc_once(slot, bytes);
     return slot;
 }
 
@@ -52,17 +49,16 @@ Workspace& workspace(ks_gauge_t g)
     if (!g->ws) g->ws = new Workspace();
     Workspace& w = *g->ws;
     const int vh = g->geom.Vh;
-    if (!w.partials) {
+    if (!w.host_scal) {
         w.npart = blocks_for(vh);
         const int cap = std::max(w.npart, dslash_max_blocks(g->geom));
-        w.partials = static_cast<double*>(device_alloc(sizeof(double) * (cap + 64)));
+        w.bytes += alloc_once(w.partials, sizeof(double) * (cap + 64));
         w.scal = w.partials + cap;
-        w.bytes += sizeof(double) * (cap + 64);
         const int nrr = blocks_for(vh, cg_step_threads(vh));
-        w.rr_part = static_cast<double*>(device_alloc(sizeof(double) * nrr));
-        w.bytes += sizeof(double) * nrr;
-        w.st = static_cast<CGState*>(device_alloc(sizeof(CGState)));
-        KS_HIP(hipHostMalloc(reinterpret_cast<void**>(&w.st_host), sizeof(CGState)));
+        w.bytes += alloc_once(w.rr_part, sizeof(double) * nrr);
+        alloc_once(w.st, sizeof(CGState));
+        if (!w.st_host)
+            KS_HIP(hipHostMalloc(reinterpret_cast<void**>(&w.st_host), sizeof(CGState)));
         KS_HIP(hipHostMalloc(reinterpret_cast<void**>(&w.host_scal), sizeof(double) * 64));
     }
     const size_t f64 = field_bytes(g->geom, KS_F64);

@@ -501,3 +501,61 @@ def test_cg_with_streamed_links_and_lanes(ks):
         runs.append((r.stats["iters"], host(x)))
     assert runs[0][0] == runs[1][0] == 40
     assert np.all(np.isfinite(runs[0][1])) and np.array_equal(runs[0][1], runs[1][1])
+
+
+def test_calls_after_ones_that_ran_out_of_memory(ks):
+    """A call that finds no room for all the buffers its handle keeps fails, whichever is the first
+    that does not fit, and the same call succeeds once there is room, with the bits of a handle
+    that never met a shortage.  (One large block fills the card throughout: taking and giving back
+    that much lasts seconds.)"""
+    import torch
+    dims = (16, 16, 16, 16)
+    g = make_gauge(dims, 0.4, 95)
+    b = gaussian_source(g.volume // 2, 96)
+    bd, w = dev(b), np.zeros(ks.NET_WEIGHTS, dtype=np.complex128)
+    w[::9] = 0.1                                # identity paths
+    xs = [zeros_dev(b.shape) for _ in range(3)]
+    par = ks.default_params(tol=1e-6, inner=ks.F32)
+
+    def run(call, G, net):
+        for x in xs:
+            x.zero_()
+        if call == "cg":
+            ks.cg_solve(G, 0.3, bd, xs[0], par)
+        elif call == "multishift":
+            ks.multishift_cg_solve(G, [0.3, 0.5, 0.9], bd, xs, 1e-6, par)
+        elif call == "loss_grad":
+            return net.loss_grad([G], [0.3], [bd], [bd])[1]
+        else:
+            net.apply(G, bd, xs[0], mfma=call == "net_mfma")
+        torch.cuda.synchronize()
+        return np.stack([host(x) for x in xs])
+
+    calls = ("cg", "multishift", "net", "net_mfma", "loss_grad")
+    ref = {c: run(c, ks.Gauge(dims, g.fat, g.naik), ks.Net(w)) for c in calls}
+    torch.cuda.empty_cache()
+    free = lambda: torch.cuda.mem_get_info()[0] >> 20
+    fill = lambda mb: torch.empty((free() - mb) << 20, dtype=torch.uint8, device="cuda")
+    rest = [fill(1200)]
+    shortages = {c: 0 for c in calls}
+    for call in calls:
+        for mb in (24, 48, 80, 120, 170):
+            G, net = ks.Gauge(dims, g.fat, g.naik), ks.Net(w)
+            torch.cuda.empty_cache()
+            filler = [fill(mb)]
+            while free() > mb + 8:              # a block may leave more than asked for
+                filler.append(fill(mb))
+            announce("out of memory", call, mb, free())
+            try:
+                run(call, G, net)
+            except ks.KSError as e:
+                assert e.code == -3, e
+                shortages[call] += 1
+            del filler
+            torch.cuda.empty_cache()
+            assert np.array_equal(run(call, G, net), ref[call])
+            G.free()
+            net.free()
+    del rest
+    torch.cuda.empty_cache()
+    assert all(shortages.values()), shortages
