@@ -75,23 +75,20 @@ BATCH_DELTA = 0.01
 BATCH_RU_BYTES = (2 * 4 * 48 + 2 * 4 * 24) + (2304 + 2 * 4 * 48) + (2304 + 4 * 4 * 48) + \
     (4 * 48 + 4 * 4 * 24)
 # network (per site of the full lattice), applied to the solver's FP32 even-site fields (24 B
-# per even site), as the flexible CG applies it.  FP32 path: four layers 1->8, 8->8, 8->8,
-# 8->1, each reading its site's 8 stored FP32 fat links (8 x 72 B) and its input channels and
-# writing its output channels (FP32 complex colour vectors, 24 B each), plus the input embedded
-# on both parities (even input read, both parities written: 12 + 24 B per site) and the even
-# output read back into the field (12 + 12 B).  Matrix-core path: binary16 links (8 x 36 B) and
-# activations (96 B per site for 8 channels); the first layer reads the even input and the odd
-# sites' links and writes both parities, the middle two read and write every site, the last
-# reads all activations and the even sites' links and writes the even output.
-_NET_F32 = sum(576 + 24 * (ci + co) for ci, co in ((1, 8), (8, 8), (8, 8), (8, 1))) + 36 + 24
+# per even site), as the flexible CG applies it.  The first layer reads the even input and the
+# odd sites' links and writes both parities, the middle two read and write every site, the last
+# reads all activations and the even sites' links and writes the even output.  FP32 path: FP32
+# links (8 x 72 B) and activations (192 B per site for 8 channels); matrix-core path: binary16
+# links (8 x 36 B) and activations (96 B).
+_NET_F32 = (12 + 288 + 192) + 2 * (192 + 576 + 192) + (192 + 288 + 12)
 _NET_MFMA = (12 + 144 + 96) + 2 * (96 + 288 + 96) + (96 + 144 + 12)
 NET_BYTES_PER_SITE = {"f32": _NET_F32, "mfma": _NET_MFMA}
-# link construction, per site: the 3x3 complex products of the two smearing levels as nested
-# (per direction 6 three-link staples and 6 outer terms of 4 inner staples, 2 products each:
-# 72; Lepage adds loads, no products), the Naik products (2 per direction), 198 flops each,
-# and the U(3) projection counted as 8 Newton steps of ~300 flops per link.  Its least data is
-# the thin links read (576 B) and the fat and Naik links written (2 x 576 B).
-HISQ_FLOPS_PER_SITE = (2 * 4 * 72 + 4 * 2) * 198 + 4 * 8 * 300
+# link construction, per site: the 3x3 complex products of the two smearing levels (per direction
+# 24 staples of 2 products each, 6 more with the Lepage term of the second level), the Naik
+# products (2 per direction), 198 flops each, and the U(3) projection counted as 5 Newton steps
+# of ~300 flops per link.  Its least data is the thin links read (576 B) and the fat and Naik
+# links written (2 x 576 B).
+HISQ_FLOPS_PER_SITE = (4 * 48 + 4 * 60 + 4 * 2) * 198 + 4 * 5 * 300
 HISQ_BYTES_PER_SITE = 3 * 576
 FP64_PEAK_TFLOPS = 78.6
 
@@ -972,8 +969,8 @@ def main():
              "least_data_GBps": HISQ_BYTES_PER_SITE * g.volume / hsec / 1e9,
              "note": "fat and Naik links from the 32^4 thin links: fat7, U(3) projection, "
                      "fat7 + Lepage, Naik, signs (FP64): far below both its FP64 and its HBM "
-                     "roofline; its passes are bound by the latency of cached neighbour-matrix "
-                     "gathers"}
+                     "roofline; its passes are bound by the neighbours' matrices that they "
+                     "fetch beyond the L2"}
     walls = [w for w, _ in batch_runs]
     per_solve = [x["seconds"] for _, st in batch_runs for x in st]
     worst = max(x["true_rel_resid"] for _, st in batch_runs for x in st)

@@ -333,8 +333,8 @@ typedef struct {
  * or 4 right-hand sides per lattice; inner: KS_F32 (FP32 inner iterations, FP64 reliable
  * updates), KS_F16 (binary16 links and vectors with an FP32 scale per site and right-hand
  * side, FP32 arithmetic, the solution's increments in FP32, FP64 reliable updates) or KS_F64.
- * Links are held in the library's per-lattice stores; vectors in arenas that keep the nrhs
- * values of a site adjacent, so one link load serves all of them.  Synchronises the
+ * Links are held in the library's per-lattice stores; vectors in arenas that hold a lattice's
+ * nrhs right-hand sides side by side, so one link load serves all of them.  Synchronises the
  * stream. */
 ks_status_t ks_batch_create(ks_batch_t* out, int nlat, const int* dims, const double* const* fat,
                             const double* const* naik, int on_device, int nrhs, ks_prec_t inner,

@@ -799,8 +799,8 @@ __global__ void batch_io_kernel(const LatDesc* __restrict__ lats, char* __restri
 
 // ---------------------------------------------------------------- launchers
 
-// Threads of the update and direction kernels' grids, which stride over the tiles: all that the chip
-// holds at two waves per SIMD.  Every block sums its lattices' partials once per lattice it meets, so
+// Most threads of the update and direction kernels' grids, which stride over the tiles (eight waves
+// per SIMD, some three times what is resident; set by measurement).  Every block sums its lattices' partials once per lattice it meets, so
 // fewer blocks than tiles pay on one large lattice (3072 tiles of 256, binary16, R = 4: 62 + 36 us
 // against 66 + 39 with a block per tile), while a batch whose tiles all fit takes a block per tile
 // (3212 tiles of 64, FP32, R = 4: 23.1 + 14.3 us, 24.5 + 16.7 with 2048 blocks).

@@ -11,7 +11,7 @@ namespace {
 
 constexpr int kFinish = 1024;
 
-// Fixed-order sum: thread t adds partials t, t + 1024, ... in order, then a fixed tree.
+// Largest of n non-negative values: thread t takes t, t + 1024, ..., then a fixed tree.
 __global__ __launch_bounds__(kFinish) void reduce_max_kernel(const double* __restrict__ in, int n,
                                                              double* __restrict__ out)
 {

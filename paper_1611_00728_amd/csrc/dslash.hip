@@ -342,7 +342,8 @@ __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
             xs[e].r = fma(b, xs[e].r, rs[e].r);
             xs[e].i = fma(b, xs[e].i, rs[e].i);
         }
-        // every lane that reads site h is of this wave and has read it
+        // every live lane that reads site h is of this wave and has read it (what a dead lane makes
+        // of site vh - 1 is dropped)
         if (live && j == 0) Spinor<P>::store(dir.p, vh, h, xs);
     }
 #pragma unroll

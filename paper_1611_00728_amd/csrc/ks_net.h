@@ -18,7 +18,9 @@ extern const int kLayerOut[4];
 size_t layer_weight_offset(int l);   // complex offset of layer l's weights
 
 // Activation and gradient buffers of one lattice size: levels 0..4 (channels 1, 8, 8, 8, 1),
-// FP32 as act_pair (8 channels) and ActPlanes (1 channel, even sites) lay them out.
+// FP32 as act_pair (8 channels) and ActPlanes (1 channel, even sites) lay them out.  act[4] and
+// grad[0] are not held: the last layer writes the caller's vector, the backward pass ends at
+// level 1's gradient.
 struct NetBuffers {
     int vh = 0;
     float2* act[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};

@@ -848,12 +848,13 @@ const int kLayerIn[4] = {1, 8, 8, 8};
 double net_model_bytes(int use_mfma, double vec_bytes)
 {
     if (use_mfma) return 2.0 * net_mfma_model_bytes_per_site(vec_bytes);
-    // per site of the full lattice each FP32 layer reads its site's eight stored links and
-    // its input channels and writes its output channels (FP32 complex colour vectors); the
-    // input is embedded on both parities and the output read back on the even sites
-    double total = 0.0;
-    for (int l = 0; l < 4; ++l) total += 8 * 72 + 24.0 * (kLayerIn[l] + kLayerOut[l]);
-    return 2.0 * total + vec_bytes + 2 * 24.0 + 24.0 + vec_bytes;
+    // per even site: the first layer reads the even input vector and the odd site's eight FP32
+    // links and writes both sites' activations, the middle two read and write every site's and
+    // read all links, the last reads both sites' activations and the even site's links and writes
+    // the even output vector
+    const double links = 8 * 72.0, act = 8 * 24.0;
+    const double first = vec_bytes + links + 2 * act, middle = 2 * (act + links + act);
+    return first + 2 * middle + 2 * act + links + vec_bytes;
 }
 const int kLayerOut[4] = {8, 8, 8, 1};
 
@@ -868,11 +869,12 @@ NetBuffers& net_buffers(NetCtx& n, const Geom& g)
 {
     NetBuffers& B = n.bufs[g.Vh];
     if (B.vh == 0) {
-        const size_t site = (size_t)2 * 3 * g.Vh * sizeof(float2);   // one channel, both parities
-        const int ch[5] = {1, 8, 8, 8, 1};
-        for (int l = 0; l < 5; ++l) {
-            if (l < 4) alloc_once(B.act[l], site * ch[l]);
-            alloc_once(B.grad[l], site * ch[l]);
+        const size_t half = (size_t)3 * g.Vh * sizeof(float2);   // one channel, one parity
+        alloc_once(B.act[0], half);
+        alloc_once(B.grad[4], half);
+        for (int l = 1; l < 4; ++l) {
+            alloc_once(B.act[l], half * 16);
+            alloc_once(B.grad[l], half * 16);
         }
         B.vh = g.Vh;
     }
