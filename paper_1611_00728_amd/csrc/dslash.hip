@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
     // the gate before anything else: after a reliable update falls due, up to check_every steps
     // are stopped here, and links read ahead of it would be read for nothing (CG with FP32 inner
     // steps, 20^4, check_every 64: 18.4 ms with one thread per site, 30.9 with the links ahead of
-    // the gate, 15.1 behind it; waiting for it costs 8^4 FP64 1 %)
+    // the gate, 15.1 behind it; waiting for it costs solves up to 12^4 1-2 %)
     double share = 0.0, beta = 0.0;
     if constexpr (kDir && !XPAY) {
         if (dir.st->s_gate) return;
