@@ -428,10 +428,14 @@ __global__ __launch_bounds__(256) void tile_links_kernel(int vol, const double2*
 }
 
 // W = V (V^+ V)^(-1/2) in place, by the scaled Newton iteration for the polar factor,
-// X <- (g X + (g X)^-+ ) / 2 with g = |det X|^(-1/3), at most kPolarIters steps; a singular or
-// non-finite V sets *bad.  The iteration converges quadratically: after a step that moved X by
-// d (relative) what is left is about d^2 / 2, so it ends at d^2 <= 1e-17.  (X^-1)^+ =
-// conj(cof X) det X / |det X|^2, cof the cofactors: one division for the nine entries.
+// X <- (g X + (g X)^-+ ) / 2 with g = |det X|^(-1/3) (1 once that is within 1e-3 of it), at most
+// kPolarIters steps; a singular or non-finite V sets *bad.  The iteration converges quadratically
+// and ends at a step that moved X by rounding only.  (X^-1)^+ = conj(cof X) det X / |det X|^2, cof
+// the cofactors; every entry is divided for itself, by one reciprocal and a residual step each: a
+// common factor's rounding turns the whole matrix, and three such matrices make a Naik link
+// (relative error of smooth links' W and Naik links, extended precision: 1.20e-16 and 2.52e-16 with
+// det X / |det X|^2 as one factor and a last step less, 1.11e-16 and 2.26e-16 this way; 32^4, all:
+// 7.51 and 7.54 ms, 7.75 with eighteen divisions).
 constexpr int kPolarIters = 40;
 
 __global__ __launch_bounds__(kBlock) void u3_project_kernel(int vol, double2* __restrict__ V,
@@ -463,22 +467,24 @@ __global__ __launch_bounds__(kBlock) void u3_project_kernel(int vol, double2* __
             ok = false;
             break;
         }
-        const double gam = it < 6 ? cbrt(1.0 / ad) : 1.0;
-        // 0.5 / gam times det / |det|^2
-        const double ih = 0.5 / (gam * d2), hg = 0.5 * gam;
-        const cxd w = {ih * det.r, ih * det.i};
+        const double gam = it < 6 && fabs(ad - 1.0) > 1e-3 ? cbrt(1.0 / ad) : 1.0;
+        const double dg = d2 * gam, rd = 1.0 / dg;
+        auto over_dg = [&](double v) {
+            const double q = v * rd;
+            return fma(fma(-q, dg, v), rd, q);
+        };
         double diff = 0.0, nrm = 0.0;
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
-            const cxd cc = {cf.e[k].r, -cf.e[k].i};
-            cxd y = {hg * X.e[k].r, hg * X.e[k].i};
-            cfma(y, cc, w);
+            const cxd p = cmul({cf.e[k].r, -cf.e[k].i}, det);
+            const cxd y = {0.5 * fma(gam, X.e[k].r, over_dg(p.r)),
+                           0.5 * fma(gam, X.e[k].i, over_dg(p.i))};
             const double dr = y.r - X.e[k].r, di = y.i - X.e[k].i;
             diff += dr * dr + di * di;
             nrm += y.r * y.r + y.i * y.i;
             X.e[k] = y;
         }
-        if (diff <= 1e-17 * nrm) break;
+        if (diff <= 1e-30 * nrm) break;
     }
     if (!ok) {
         *bad = 1;
