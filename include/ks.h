@@ -303,7 +303,7 @@ ks_status_t ks_force(ks_gauge_t g, int nterm, const double* residues, const doub
  * for HISQ.  thin_dev, fat_dev, naik_dev: device complex128 [4][V][3][3] (layout of
  * ks_gauge_load), distinct.  KS_ERR_NONFINITE when a level-1 link is singular.  Its scratch
  * (32 fields of one direction's links, 4.8 GB at 32^4; 14 where those would take over 32 GiB or
- * the device has no room) is allocated on the first call on a device and kept for later calls
+ * while the device has no room) is allocated on the first call on a device and kept for later calls
  * (grown for a larger lattice) until ks_hisq_release; calls that overlap in time on one device
  * share it and race.  Synchronises the stream. */
 ks_status_t ks_hisq_links(const int dims[4], const double* thin_dev, double* fat_dev,

@@ -16,7 +16,7 @@
 //     F   = c1 U + sum_l (S_{+l} + S_{-l})[I_l] + cL sum_a S_a[S_a[U]],
 // three passes of 6, 12 and 6 staples (the Lepage staples are formed again in the last).  Building
 // every middle field in registers at the outer staple's end instead takes 6 + 24 + 6 staples and
-// twelve launches per mu: 30.3 ms for both smearings at 32^4, 7.4 ms in three passes.
+// twelve launches per mu: 30.3 ms for both smearings at 32^4, 7.5 ms in three passes.
 // The passes run two waves per SIMD and are bound by the matrices they fetch beyond the XCD's L2
 // (five-link pass 11.8 GB in 1.55 ms in plain order, 7.6 TB/s; see smear_place).
 #include <map>
@@ -552,7 +552,7 @@ namespace {
 //
 // All four directions share a pass (32 fields) up to this size, a ninth of the card's memory
 // (48^3 x 64 takes 30.4 GiB); larger lattices take a direction per pass (32^4: 9.6 ms instead of
-// 7.4), so that they need no more memory than their 14 fields.
+// 7.5), so that they need no more memory than their 14 fields.
 constexpr size_t kWideScratch = (size_t)32 << 30;
 
 struct HisqScratch {
